@@ -152,8 +152,8 @@ int mrpie_workspace_size(const mrpie_problem* pb, const mrpie_params* pr, size_t
  * and the measured detector amplitude), then all J pairs are registered
  * and the Adam step is taken, in order on `stream`.  Subpixel moves,
  * refinement and the near-field propagator run the four-launch position
- * step; the plain far-field sweep runs two launches per position (or one
- * workgroup per job for probes whose modes fit the LDS).  No device memory
+ * step; the plain far-field sweep runs as one persistent launch, or as two
+ * launches per position where those are faster.  No device memory
  * is allocated. */
 int mrpie_rpie(const mrpie_problem* pb, const mrpie_params* pr, void* obj, void* probe,
                float* pos, float* adam, const float* intens, float* err_out, int32_t* status,
@@ -202,12 +202,10 @@ typedef struct {
  * stages of the row / column pass (radix 4: more threads per transform,
  * shorter latency; radix 8: fewer stages, less LDS traffic); rows_threads:
  * 256 or 512 threads per row workgroup; lds_sweep in [0, 8]: a job with
- * M <= lds_sweep whose modes fit the LDS together (M N^2 <= 16384: 32^2
- * with up to 8 modes, 64^2 with up to 4, 128^2 with 1) runs as one
- * workgroup that keeps the probe in registers and the 2-D FFT in LDS for
- * the whole call; other jobs run the row / column passes (default for
- * single-job calls: 8 for N = 32, 1 for N = 64, 0 otherwise; 0 in batches,
- * where small jobs ride along in the shared launches); cols_width: 1 or 4 adjacent detector
+ * M <= lds_sweep whose modes fit one workgroup's LDS together (M N^2 <=
+ * 16384: 32^2 with up to 8 modes, 64^2 with up to 4, 128^2 with 1) runs the
+ * whole call in one persistent launch instead of the row / column passes;
+ * cols_width: 1 or 4 adjacent detector
  * columns per column-pass workgroup (1: shortest latency for a single
  * sweep; 4: coalesced 32-byte row segments, for batches); rows_inplace: 1
  * runs the inverse row FFTs of multi-job launches in place (half the row
@@ -221,7 +219,11 @@ typedef struct {
  * launches per position, less memory traffic); 0 fuses them into one row
  * pass (two launches per position; single-job calls always fuse).  The
  * installed setting is process-wide host state (guarded by a lock); results
- * do not depend on it beyond float rounding.  mrpie_autotune times the candidates on the device and installs
+ * do not depend on it beyond float rounding.  Without an installed setting
+ * (or with the default installed) the library runs most calls as one
+ * persistent launch of teams of workgroups (see mrpie_rpie_batched); a setting
+ * other than the default, for the size of a call's largest probe, asks for
+ * launches of that shape.  mrpie_autotune times the candidates on the device and installs
  * the fastest.  mrpie_set_tuning with M = 0 sets every mode class of
  * (N, batched); mrpie_get_tuning takes M in [1, 8]. */
 typedef struct {
@@ -233,7 +235,11 @@ int mrpie_get_tuning(int32_t N, int32_t M, int32_t batched, mrpie_tuning* t);
 /* Batched M-rPIE: runs mrpie_rpie's sweep (same parameters for every job;
  * refine, subpixel and propagator must be 0, else MRPIE_EUNSUPPORTED) on
  * `njobs` independent reconstructions of any mix of N, M, J and object
- * size, lock-step by position: every launch advances one position of every
+ * size.  By default most calls run as one persistent launch: the workgroups
+ * of each XCD form teams that take jobs from a queue, largest first, and run
+ * each from its first position to its last.  The others (probes of 192^2 in
+ * large numbers, 7 or 8 modes, installed or passed tunings) advance lock-step
+ * by position: every launch advances one position of every
  * running job, so one pair of launches carries the work of many jobs.  The
  * jobs of a stream run in at most 36 launch lanes (the job table of one
  * launch); a share of more than 36 jobs is dealt to the lanes longest job
@@ -242,15 +248,14 @@ int mrpie_get_tuning(int32_t N, int32_t M, int32_t batched, mrpie_tuning* t);
  * probe, workspace or error-curve memory (positions and intensities are
  * only read and may be shared; so may status words).
  * Each job's object and probe match those of a mrpie_rpie call on that job
- * alone to float rounding (the single-job column pass keeps its first and
- * last FFT stages in registers; jobs that run the one-workgroup LDS sweep in
- * both are bitwise equal); the error curve may differ in the summation
- * order of its partial sums.  With two or more jobs, every second job runs
+ * alone to float rounding; the error curve may differ in the summation
+ * order of its partial sums.  Persistent launches of one device run one at a
+ * time: a call on another stream waits for the last one (not under capture).
+ * Of two or more jobs for the lock-step launches every second one runs
  * on an internal non-blocking stream (default priority; the first such call
  * on a device creates it and 16 events, kept until the process ends),
  * forked from `stream` and joined back into it before the call returns, so
- * two lock-step launch sequences share the GPU (jobs whose modes fit the
- * LDS run their one-workgroup sweep there too); while `stream` is being
+ * two lock-step launch sequences share the GPU; while `stream` is being
  * captured into a graph, all launches stay on `stream`.  `jobs` is a HOST
  * array read during the call.  `tuning` (may be NULL) sets the launch shape
  * of every launch of this call; NULL uses the installed tuning of each
@@ -270,7 +275,8 @@ int mrpie_rpie_batched(int32_t njobs, const mrpie_job* jobs, const mrpie_params*
  * up), timed with HIP events, keeps each candidate's fastest timed run,
  * installs the best
  * candidate for that (N, mode class, batch class) as mrpie_set_tuning
- * would, and returns it in *best (may be NULL).  cand_ms (may be NULL)
+ * would, and returns it in *best (may be NULL).  The persistent launch is
+ * timed too; where it is faster than every candidate it stays the default.  cand_ms (may be NULL)
  * receives each candidate's time in ms.  The call waits on the host for its
  * timing events, so it may not be captured into a graph; it allocates no
  * device memory (workspace: mrpie_autotune_workspace_size bytes, reps in
@@ -357,15 +363,15 @@ int mrpie_canvas(const mrpie_problem* pb, const void* probe, const float* pos, f
  * = 0 switches timing off).  Classes: 0 = sweep row pass (k_rows, k_rows1),
  * 1 = sweep column pass (k_cols, k_cols1), 2 = registration column pass
  * (k_reg_cols), 3 = registration window GEMM (k_reg_gemm1), 4 = adjoint
- * modulus pass (k_adj_p3), 5 = one-workgroup LDS sweep (k_lds_sweep),
- * 6 = split update pass (k_upd), 7 = split gather pass (k_gat).
+ * modulus pass (k_adj_p3), 5 = not used, 6 = split update pass (k_upd),
+ * 7 = split gather pass (k_gat), 8 = persistent sweep (k_team).
  * The events are created without the system-scope fence, which would
  * otherwise write the L2 back inside the timed dispatch.
  * mrpie_timing_read(avg_ms[nkinds], count[nkinds], avg_units[nkinds],
  * nkinds): waits for the recorded events, returns the mean duration, the
  * number of timed launches and the mean number of units those launches
- * process (jobs per sweep pass, positions per adjoint pass, pairs per
- * registration pass;
+ * process (jobs per sweep pass, positions per adjoint pass and per
+ * persistent sweep, pairs per registration pass;
  * avg_units may be NULL) per class, and clears the record.  Host-side
  * state, one per process. */
 int mrpie_timing_enable(int32_t stride);

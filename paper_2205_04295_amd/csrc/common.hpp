@@ -200,7 +200,7 @@ std::mutex& side_mutex();
 // a start / stop event pair, so the events carry that dispatch's own start
 // and end time on its stream; mrpie_timing_read() averages them.
 enum TimedKernel {
-  TK_ROWS = 0, TK_COLS = 1, TK_REG = 2, TK_GEMM = 3, TK_ADJ = 4, TK_LDS = 5, TK_UPD = 6, TK_GAT = 7, TK_COUNT = 8
+  TK_ROWS = 0, TK_COLS = 1, TK_REG = 2, TK_GEMM = 3, TK_ADJ = 4, TK_LDS = 5, TK_UPD = 6, TK_GAT = 7, TK_TEAM = 8, TK_COUNT = 9
 };
 struct TimedLaunch {
   hipEvent_t start = nullptr, stop = nullptr;

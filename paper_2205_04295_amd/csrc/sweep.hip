@@ -1180,13 +1180,8 @@ __global__ void k_probe_back(const LaunchArgs a) {
 
 // ------------------------------------------------------------ tuning
 // Launch shapes of the sweep, per (N, batch class): FFT radix plan of each
-// pass, threads per row workgroup, and up to which mode count a job whose
-// modes fit the LDS runs the one-workgroup sweep.  The defaults were the
-// fastest measured on MI355X: radix 8 in both passes with 256 threads for
-// 256^2 x 3; the one-workgroup sweep for 32^2 (5 modes: 9.3 against 12.9 us
-// per position) and 64^2 x 1 (9.6 against 11.6 us), the passes from 64^2 x 3
-// (13.3 against 20.0 us) and 128^2 x 1 (12.3 against 42.3 us) on, where one
-// CU's vector ALUs and LDS bandwidth bound the one-workgroup sweep; one
+// pass, threads per row workgroup.  The defaults were the fastest measured on
+// MI355X: radix 8 in both passes with 256 threads for 256^2 x 3; one
 // detector column per column workgroup for a single sweep (19.5 against
 // 23.3 us per position at 256^2 x 3), four in batches (8 jobs: 52.1 against
 // 57.2 us per lock-step position, 32 jobs: 168 against 182 us); in-place
@@ -1197,7 +1192,7 @@ __global__ void k_probe_back(const LaunchArgs a) {
 // single-job kernels' register capacities; the multi-job kernels split the
 // last class into 5-6 and 7-8).
 static Tuning g_tune[5][4][3];
-static bool g_tune_set[5][4][3];
+static bool g_tune_set[5][4][3], g_tune_team[5][4][3];
 static std::mutex g_tune_mu;
 
 // Call classes: a single job, batches of 2 to kLargeBatch - 1 jobs, larger
@@ -1207,12 +1202,7 @@ static int batch_class(int nb) { return nb <= 1 ? 0 : nb < kLargeBatch ? 1 : 2; 
 int batch_class_jobs(int cls) { return cls <= 0 ? 1 : cls == 1 ? 2 : kLargeBatch; }
 static int mode_index(int M) { return M <= 1 ? 0 : M <= 2 ? 1 : M <= 4 ? 2 : 3; }
 
-// The one-workgroup LDS sweep is the default for a single small job only: in
-// a batch, small jobs ride along in the shared row / column launches, which
-// the other jobs' launches pay for anyway (uneven 64-job batch: 439k -> 480k
-// positions x iterations / s eager, 310k -> 337k as a replayed graph, where
-// the LDS sweep's long single launch would otherwise run ahead of the passes
-// on the one stream).
+// (Without an installed tuning the teams take most calls: see choose_team.)
 Tuning default_tuning(int N, int nb) {
   const int bc = batch_class(nb);
   const int lds = bc ? 0 : N == 32 ? MRPIE_MAX_MODES : N == 64 ? 1 : 0;
@@ -1234,7 +1224,28 @@ void set_tuning(int N, int M, int nb, const Tuning& t) {
     if (M <= 0 || mi == mode_index(M)) {
       g_tune[ni][mi][bc] = t;
       g_tune_set[ni][mi][bc] = true;
+      g_tune_team[ni][mi][bc] = false;
     }
+}
+
+static bool same_tuning(const Tuning& a, const Tuning& b) {
+  return a.rows_radix == b.rows_radix && a.cols_radix == b.cols_radix && a.rows_threads == b.rows_threads &&
+         a.lds_sweep == b.lds_sweep && a.cols_width == b.cols_width && a.rows_inplace == b.rows_inplace &&
+         a.rows_split == b.rows_split;
+}
+
+bool tuned(int N, int M, int nb) {
+  const int ni = n_index(N), mi = mode_index(M), bc = batch_class(nb);
+  std::lock_guard<std::mutex> lk(g_tune_mu);
+  return ni >= 0 && g_tune_set[ni][mi][bc] && !g_tune_team[ni][mi][bc] &&
+         !same_tuning(g_tune[ni][mi][bc], default_tuning(N, nb));
+}
+
+void prefer_team(int N, int M, int nb) {
+  const int ni = n_index(N), mi = mode_index(M), bc = batch_class(nb);
+  if (ni < 0) return;
+  std::lock_guard<std::mutex> lk(g_tune_mu);
+  g_tune_team[ni][mi][bc] = true;
 }
 
 // ------------------------------------------------------------ host driver
@@ -1499,24 +1510,63 @@ static int run_passes(const Common& c, const JobRec* jobs, int njobs, float* con
   return MRPIE_OK;
 }
 
-// Jobs whose modes fit the LDS (and whose tuning allows it) run the
-// one-workgroup sweep; the rest run the row / column passes.  With two or
-// more jobs the call forks the library's side stream from `s` (after the
-// twiddle tables are written on `s`) and joins it back at the end: the LDS
-// sweep and every second job of the passes run there, the rest on `s`.
-// Under stream capture everything stays on `s`: a replayed graph of one
+// Which jobs of a call run in teams (team.hip).  A tuning that the caller
+// passed, or installed for a job's size or the call's largest, asks for
+// launches of that shape: such a job goes to a team only if the tuning's lds_sweep says so.  The others go
+// where team_suits() has them; a call of mixed probe sizes goes to the teams
+// as a whole unless most of its work does not suit them (64 uneven jobs of
+// 64^2 to 256^2: 9.9 ms in teams, 11.8 ms in launches, 192^2 jobs included).
+static void choose_team(const JobRec* jobs, int njobs, const Tuning* force, std::vector<char>& team) {
+  double work = 0.0, unsuited = 0.0;
+  bool mixed = false;
+  int maxN = 0, maxM = 1;  // the launches take the tuning of the largest
+  for (int b = 0; b < njobs; ++b) {
+    maxN = std::max(maxN, jobs[b].N);
+    maxM = std::max(maxM, jobs[b].M);
+  }
+  const bool asked = force || tuned(maxN, maxM, njobs);
+  team.assign(njobs, 0);
+  std::vector<char> free_choice(njobs, 0);
+  for (int b = 0; b < njobs; ++b) {
+    const JobRec& jb = jobs[b];
+    if (!team_fits(jb.N, jb.M)) continue;
+    if (asked || tuned(jb.N, jb.M, njobs)) {
+      const int most = force ? force->lds_sweep : get_tuning(jb.N, jb.M, njobs).lds_sweep;
+      team[b] = jb.M <= most && lds_sweep_fits(jb.N, jb.M);
+      continue;
+    }
+    free_choice[b] = 1;
+    team[b] = team_suits(jb.N, jb.M, njobs);
+    mixed |= jb.N != jobs[0].N;
+    const double w = (double)jb.J * jb.T * jb.M * jb.N * jb.N;
+    work += w;
+    if (!team[b]) unsuited += w;
+  }
+  if (!mixed) return;
+  for (int b = 0; b < njobs; ++b)
+    if (free_choice[b]) team[b] = 2.0 * unsuited <= work;
+}
+
+// Jobs go to the teams (one persistent launch) or through the row / column
+// passes.  With two or more jobs for the passes the call forks the library's
+// side stream from `s` (after the twiddle tables are written on `s`) and joins
+// it back at the end: every second job of the passes runs there, the rest on
+// `s`.  Under stream capture everything stays on `s`: a replayed graph of one
 // launch chain is faster than one of two interleaved chains (8 jobs at
 // 256^2 x 3: 204k against 146k positions x iterations / s).
 int run_sweep(const Common& c, const JobRec* jobs, int njobs, float* const* err_out, hipStream_t s,
               const Tuning* force) {
-  std::vector<JobRec> lj, pj;
-  std::vector<float*> le, pe;
+  std::vector<JobRec> tj, pj;
+  std::vector<float*> te, pe;
+  std::vector<char> team;
+  choose_team(jobs, njobs, force, team);
   for (int b = 0; b < njobs; ++b) {
-    const JobRec& jb = jobs[b];
-    const int lds_max = force ? force->lds_sweep : get_tuning(jb.N, jb.M, njobs).lds_sweep;
-    const bool lds = jb.M <= lds_max && lds_sweep_fits(jb.N, jb.M);
-    (lds ? lj : pj).push_back(jb);
-    (lds ? le : pe).push_back(err_out ? err_out[b] : nullptr);
+    (team[b] ? tj : pj).push_back(jobs[b]);
+    (team[b] ? te : pe).push_back(err_out ? err_out[b] : nullptr);
+  }
+  if (!tj.empty()) {
+    const int rc = run_team(c, tj.data(), (int)tj.size(), te.data(), s);
+    if (rc || pj.empty()) return rc;
   }
   int rc = launch_init_twiddles(s);
   if (rc) return rc;
@@ -1525,16 +1575,14 @@ int run_sweep(const Common& c, const JobRec* jobs, int njobs, float* const* err_
   std::unique_lock<std::mutex> lk;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   MRPIE_HIP(hipStreamIsCapturing(s, &cap));
-  if (njobs >= 2 && cap == hipStreamCaptureStatusNone) {
+  if (pj.size() >= 2 && cap == hipStreamCaptureStatusNone) {
     rc = side_stream(&s2, &ev);
     if (rc) return rc;
     lk = std::unique_lock<std::mutex>(side_mutex());
     MRPIE_HIP(hipEventRecord(ev[0], s));
     MRPIE_HIP(hipStreamWaitEvent(s2, ev[0], 0));
   }
-  if (!lj.empty()) rc = run_lds_sweep(c, lj.data(), (int)lj.size(), le.data(), s2 ? s2 : s);
-  if (!rc && !pj.empty())
-    rc = run_passes(c, pj.data(), (int)pj.size(), pe.data(), s, pj.size() >= 2 ? s2 : nullptr, force);
+  rc = run_passes(c, pj.data(), (int)pj.size(), pe.data(), s, s2, force);
   if (s2) {  // joined also after an error, so `s` never runs ahead of the side stream's work
     MRPIE_HIP(hipEventRecord(ev[1], s2));
     MRPIE_HIP(hipStreamWaitEvent(s, ev[1], 0));

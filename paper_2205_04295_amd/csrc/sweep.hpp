@@ -69,8 +69,8 @@ struct Tuning {
   int rows_radix;    // 4 or 8: FFT plan of the row pass
   int cols_radix;    // 4 or 8: FFT plan of the column pass
   int rows_threads;  // 256 or 512 threads per row workgroup
-  int lds_sweep;     // jobs with M <= lds_sweep whose modes fit the LDS run the
-                     // one-workgroup sweep (0: never)
+  int lds_sweep;     // jobs with M <= lds_sweep whose modes fit one workgroup's
+                     // LDS (M N^2 <= 16384) run the team sweep (0: never)
   int cols_width;    // 1 or 4 adjacent detector columns per column workgroup
   int rows_inplace;  // 1: multi-job row passes run their inverse FFTs in place
   int rows_split;    // 1: multi-job calls run the update and the gather row
@@ -80,6 +80,12 @@ struct Tuning {
 // for it, else the default.  set_tuning with M = 0 sets every mode class.
 Tuning get_tuning(int N, int M, int nb);
 void set_tuning(int N, int M, int nb, const Tuning& t);
+// Whether a tuning other than the default is installed there that asks for
+// launches of that shape; prefer_team(true) withdraws the request (the tuning
+// stays readable) until the next set_tuning.
+bool tuned(int N, int M, int nb);
+void prefer_team(int N, int M, int nb);
+inline bool lds_sweep_fits(int N, int M) { return N <= 128 && M * N * N <= 16384; }
 Tuning default_tuning(int N, int nb);
 // A job count of call class cls (0: one job, 1: 2-15 jobs, 2: 16 or more).
 int batch_class_jobs(int cls);
@@ -111,10 +117,13 @@ int run_refining_sweep(const Common& c, const JobRec& jb, const mrpie_params* pr
 void launch_zero_err(const LaunchArgs& a, int nb, hipStream_t s);
 void launch_finish(const LaunchArgs& a, int nb, float* const* err_out, hipStream_t s, bool probe_back = true);
 
-// One-workgroup sweep of jobs whose M modes of N x N fit the LDS together
-// (M N^2 <= 16384); every job of `jobs` must fit.
-bool lds_sweep_fits(int N, int M);
-int run_lds_sweep(const Common& c, const JobRec* jobs, int njobs, float* const* err_out, hipStream_t s);
+// The sweep of whole jobs as one persistent launch (team.hip): teams of
+// workgroups, one XCD each, run a job from its first position to its last.
+// team_fits: whether a team can hold a job of M modes of N^2; team_suits:
+// whether it is also the faster way in a call of `njobs` such jobs.
+bool team_fits(int N, int M);
+bool team_suits(int N, int M, int njobs);
+int run_team(const Common& c, const JobRec* jobs, int njobs, float* const* err_out, hipStream_t s);
 
 // Host driver: runs `T` iterations (per job) of the sweep for every job in
 // `jobs` (any mix of N and M), lock-step by position: tick t performs the

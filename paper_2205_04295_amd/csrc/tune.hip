@@ -1,7 +1,7 @@
 // Autotuner of the sweep's launch shapes (FFT radix plan per pass, threads
 // per row workgroup, detector columns per column workgroup, in-place FFTs in
-// batches, and the one-workgroup LDS sweep for probes whose modes fit the
-// LDS), per probe size N, mode class of M and batch class.  It times every
+// batches, and the persistent sweep against them), per probe size N, mode
+// class of M and batch class.  It times every
 // candidate on a synthetic problem of the requested shape, on the device,
 // and installs the fastest.  Only the timing matters: the synthetic data
 // (a hash of the element index) are well-conditioned but meaningless.
@@ -151,7 +151,6 @@ int mrpie_autotune(int32_t N, int32_t M, int32_t batch, int32_t J, int32_t reps,
   const bool batched = batch > 1;
   const int n = candidates(N, M, batched, cands);
   const int nb = batch;  // the call class of `batch` jobs
-  const Tuning saved = get_tuning(N, M, nb);
   hipEvent_t e0 = nullptr, e1 = nullptr;
   MRPIE_HIP(hipEventCreate(&e0));
   if (hipEventCreate(&e1) != hipSuccess) {
@@ -162,12 +161,14 @@ int mrpie_autotune(int32_t N, int32_t M, int32_t batch, int32_t J, int32_t reps,
   // round, each candidate keeping its best time: a drift of the clocks
   // during the run then shifts every candidate alike instead of favouring
   // the ones timed while the GPU ran fastest.
-  std::vector<float> t_best((size_t)n, 0.f);
+  const int nt = n + (team_fits(N, M) ? 1 : 0);  // and the teams, which no candidate describes
+  std::vector<float> t_best((size_t)nt, 0.f);
   for (int r = 0; r <= reps && rc == MRPIE_OK; ++r) {
-    for (int i = 0; i < n && rc == MRPIE_OK; ++i) {
-      set_tuning(N, M, nb, cands[i]);
+    for (int i = 0; i < nt && rc == MRPIE_OK; ++i) {
       hipError_t e = hipEventRecord(e0, s);
-      if (e == hipSuccess) rc = run_sweep(c, jobs.data(), batch, nullptr, s);
+      if (e == hipSuccess)
+        rc = i < n ? run_sweep(c, jobs.data(), batch, nullptr, s, &cands[i])
+                   : run_team(c, jobs.data(), batch, nullptr, s);
       if (rc == MRPIE_OK && e == hipSuccess) e = hipEventRecord(e1, s);
       if (rc == MRPIE_OK && e == hipSuccess) e = hipEventSynchronize(e1);
       float ms = 0.f;
@@ -187,12 +188,10 @@ int mrpie_autotune(int32_t N, int32_t M, int32_t batch, int32_t J, int32_t reps,
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  if (rc != MRPIE_OK || best_i < 0) {
-    set_tuning(N, M, nb, saved);
-    return rc ? rc : fail(MRPIE_EDEVICE, "no candidate ran");
-  }
+  if (rc != MRPIE_OK || best_i < 0) return rc ? rc : fail(MRPIE_EDEVICE, "no candidate ran");
   const Tuning& t = cands[best_i];
   set_tuning(N, M, nb, t);
+  if (nt > n && t_best[n] <= best_ms) prefer_team(N, M, nb);
   if (best)
     *best = mrpie_tuning{t.rows_radix, t.cols_radix, t.rows_threads, t.lds_sweep, t.cols_width, t.rows_inplace,
                          t.rows_split};

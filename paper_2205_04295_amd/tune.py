@@ -31,7 +31,7 @@ def candidates(N, M, batched):
     return [_as_dict(arr[i]) for i in range(n)]
 
 
-# every launch shape of the row / column passes (the LDS sweep off): the
+# every launch shape of the row / column passes (lds_sweep off): the
 # single-sweep candidates plus the in-place and split options of batches
 CANDIDATES = [dict(rows_radix=rr, cols_radix=cr, rows_threads=th, lds_sweep=0, cols_width=cw, rows_inplace=ip,
                    rows_split=sp)
@@ -47,8 +47,8 @@ def call_class(jobs):
 
 
 def lds_fits(N, M):
-    """True when the M modes of an N x N probe fit the LDS together (the
-    one-workgroup sweep applies)."""
+    """True when the M modes of an N x N probe fit the LDS together (a
+    tuning's lds_sweep applies)."""
     return N <= 128 and M * N * N <= 16384
 
 
