@@ -17,6 +17,8 @@
 //   k_reg_gemm1  T = K (X . e^{2 pi i k.s0/N})   [U x N] x [N x N]
 //   k_reg_gemm2  C = T K^T, per-tile first maximum of |C|^2
 //   k_reg_final  window argmax (u*, v*) -> shift s0 + ((u*, v*) - c)/up
+// (windows from 32 samples on: k_reg_fold, k_reg_fold1 and k_reg_fold2 for the
+// two GEMMs, a quarter of the multiplications by symmetry, on matrix cores)
 // with K[u][k] = exp(+2 pi i k (u - c) / (N up)), k the signed frequency,
 // U = ceil(1.5 up), c = floor(U/2): the coarse lag is folded into X as a
 // diagonal phase so one K serves every pair.
@@ -198,18 +200,13 @@ __global__ void k_reg_kmat(const RegArgs a, int N) {
   }
 }
 
-// Register blocks of the two GEMMs: RB = 4 (64 x 64 output tiles, 16
-// complex FMAs per 8 LDS reads) for large windows, RB = 2 (32-row tiles)
-// for small ones, whose last 64-row tile would be mostly empty (upsample
-// 1000, 256 pairs: 28.6 against 35.0 ms; upsample 100: 1.77 against 1.82
-// ms with RB = 2).  Every output sums its terms in k order whatever RB is.
-inline int gemm_rb(int U) { return U > 320 ? 4 : 2; }
-
+// The two GEMMs as plain vector code, for windows too small for the folded
+// ones below.  Register blocks of 2 x 4 and 2 x 2.
 // T[b][u][kx] = sum_ky K[u][ky] X[b][ky][kx] e^{2 pi i (ky s0y + kx s0x)/N}
-// Tile: 16 RB u x 64 kx per workgroup, ky in chunks of 16 staged in LDS;
-// each of the 16 x 16 threads accumulates an RB x 4 block.
-constexpr int G1_RJ = 4, G1_TX = 16 * G1_RJ, G1_KC = 16;
-template <int N, int G1_RI>
+// Tile: 32 u x 64 kx per workgroup, ky in chunks of 16 staged in LDS;
+// each of the 16 x 16 threads accumulates a 2 x 4 block.
+constexpr int G1_RI = 2, G1_RJ = 4, G1_TX = 16 * G1_RJ, G1_KC = 16;
+template <int N>
 __global__ __launch_bounds__(256) void k_reg_gemm1(const RegArgs a) {
   constexpr int G1_TU = 16 * G1_RI;
   __shared__ double2 Ks[G1_TU][G1_KC + 1];
@@ -274,9 +271,9 @@ __global__ __launch_bounds__(256) void k_reg_gemm1(const RegArgs a) {
 }
 
 // C[b][u][v] = sum_kx T[b][u][kx] K[v][kx]; per-tile first maximum of |C|^2.
-// Tile 16 RB u x 16 RB v, kx in chunks of 16; each thread an RB x RB block.
-constexpr int G2_KC = 16;
-template <int N, int G2_R>
+// Tile 32 u x 32 v, kx in chunks of 16; each thread a 2 x 2 block.
+constexpr int G2_KC = 16, G2_R = 2;
+template <int N>
 __global__ __launch_bounds__(256) void k_reg_gemm2(const RegArgs a) {
   constexpr int G2_T = 16 * G2_R;
   __shared__ double2 Ts[G2_T][G2_KC + 1];
@@ -340,16 +337,288 @@ __global__ __launch_bounds__(256) void k_reg_gemm2(const RegArgs a) {
   }
 }
 
+// ------------------------------------------------- the GEMMs by symmetry
+// With w = u - c the window is symmetric, and K[c + w][k] = e^{i th k w}, th =
+// 2 pi / (N up).  Over the pairs of frequencies +-k a sum against K is
+//   sum_k e^{i th k w} x_k = E + i O,   E = sum_{k = 0..N/2} cos(th k w) p_k,
+//                                       O = sum_{k = 1..N/2} sin(th k w) m_k,
+// p_k = x_k + x_-k, m_k = x_k - x_-k (p_0 = x_0; the one term of frequency
+// -N/2 is p = x, m = -x), and the sample at -w is E - i O.  cos and sin are
+// real and one product serves two samples, so a dimension costs a quarter of
+// the multiplications of the complex product.  X is folded in both
+// dimensions at once (k_reg_fold), which leaves two products of the same form:
+//   k_reg_fold1  rows: the folds of X (kx = p of 0..N/2, then m of 1..N/2),
+//                summed over ky; columns: w of u
+//   k_reg_fold2  rows: u; summed over kx; columns: w of v; first maximum
+// Both run on the fp64 matrix cores (16 x 16 x 4).  Everything is kept in the
+// order in which the lanes of an operand take it, so that all operand loads
+// are consecutive and need no LDS:
+//   rows   of 16: [step][lane] (re, im) of row lane % 16, slot 4 step + lane / 16,
+//          first the SE steps of the even slots (k = 0..N/2, then zeros), then
+//          the SO steps of the odd ones (k = 1..N/2)
+//   table  of 16 w: [step][lane] cos or sin, likewise
+// A result tile holds, in register r, row 4 r + lane / 16 and column lane %
+// 16: as a row operand of the second product (its rows are the first one's
+// columns) register r of tile t is step 4 t + r, lane by lane.
+//
+// A wave takes 2 row tiles x JT column tiles, 16 instructions of 64 cycles a
+// step for 8 operand loads, fetched one step ahead, so the matrix cores bound
+// it.  (2 x 4 tiles need more than 256 registers, and the compiler then moves
+// accumulators between the two register files at every instruction.)  32 pairs
+// of 256^2 at upsample 1000 (window 1500): fold + fold1 + fold2 20 + 192 + 766
+// us (50 TFLOP/s of fp64 in fold2) where the complex products took 616 +
+// 3530; 400 pairs at upsample 100 (window 150): 151 + 348 + 191 us, before
+// 950 + 607.
+using d2 = double __attribute__((ext_vector_type(2)));
+using d4 = double __attribute__((ext_vector_type(4)));
+
+constexpr int JT = 2;
+
+template <int N>
+struct Fold {
+  static constexpr int SE = N / 8 + 1, SO = N / 8;         // steps of 4 slots
+  static constexpr int PT = N / 32 + 1, RT = PT + N / 32;  // row tiles of p, of p and m
+  static constexpr int TILE = (SE + SO) * 64;              // of lane operands
+  static constexpr int HOME = N * N / TILE;                // row tiles that fit a pair's work[0]
+};
+
+// Row tile t of the folded X of pair b: in work[0], the last ones behind.
+template <int N>
+__device__ __forceinline__ d2* fold_tile(const RegArgs& a, int b, int t) {
+  using F = Fold<N>;
+  return t < F::HOME ? (d2*)(a.work + (size_t)b * 2 * N * N) + (size_t)t * F::TILE
+                     : (d2*)a.F + ((size_t)b * (F::RT - F::HOME) + (t - F::HOME)) * F::TILE;
+}
+
+// The table of all column tiles, w < 16 tiles.
+template <int N>
+__global__ __launch_bounds__(256) void k_reg_table(const RegArgs a, int tiles) {
+  using F = Fold<N>;
+  double* const tab = (double*)a.K;
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < tiles * F::TILE; i += gridDim.x * 256) {
+    const int lane = i & 63, step = i / 64 % (F::SE + F::SO), w = i / F::TILE * 16 + (lane & 15);
+    const bool odd = step >= F::SE;
+    const int k = odd ? 4 * (step - F::SE) + (lane >> 4) + 1 : 4 * step + (lane >> 4);
+    double s, c;
+    sincospi(2.0 * (double)k * (double)w / ((double)N * (double)a.up), &s, &c);
+    tab[i] = k > N / 2 ? 0.0 : odd ? s : c;
+  }
+}
+
+template <int N>
+__global__ __launch_bounds__(256) void k_reg_fold(const RegArgs a) {
+  using F = Fold<N>;
+  constexpr int HN = N / 2, LW = 16 * F::PT;
+  __shared__ double2 tw[N];  // exp(-2 pi i e / N)
+  load_twiddles<N>(tw);
+  __syncthreads();
+  const int b = blockIdx.y, i = blockIdx.x * 256 + threadIdx.x;
+  const int k = i / LW, l = i - k * LW;
+  if (k >= 4 * F::SE) return;
+  const double2* const X = a.work + ((size_t)b * 2 + 1) * N * N;
+  const int s0y = a.s0[2 * b], s0x = a.s0[2 * b + 1];
+  // x[ky][kx] e^{2 pi i (ky s0y + kx s0x) / N} at (+-k, +-l)
+  const double2 z = make_double2(0.0, 0.0);
+  double2 pp = z, np = z, pn = z, nn = z;
+  if (k <= HN && l <= HN) {
+    int e = (k * s0y + l * s0x) % N, g = (l * s0x - k * s0y) % N;
+    e += e < 0 ? N : 0;
+    g += g < 0 ? N : 0;
+    const bool ky = k > 0 && k < HN, lx = l > 0 && l < HN;
+    pp = cmulc(X[k * N + l], tw[e]);
+    if (ky) np = cmulc(X[(N - k) * N + l], tw[g]);
+    if (lx) pn = cmul(X[k * N + N - l], tw[g]);
+    if (ky && lx) nn = cmul(X[(N - k) * N + N - l], tw[e]);
+  }
+  const double sk = k == HN ? -1.0 : 1.0, sl = l == HN ? -1.0 : 1.0;
+  const auto put = [&](int row, int step, int slot, double x, double y) __attribute__((always_inline)) {
+    fold_tile<N>(a, b, row >> 4)[step * 64 + (slot & 3) * 16 + (row & 15)] = d2{x, y};
+  };
+  const auto rows = [&](int step, int slot, double2 p, double2 n) __attribute__((always_inline)) {
+    put(l, step, slot, p.x + n.x, p.y + n.y);
+    if (l >= 1 && l <= HN) put(LW + l - 1, step, slot, sl * p.x - n.x, sl * p.y - n.y);
+  };
+  rows(k >> 2, k, make_double2(pp.x + np.x, pp.y + np.y), make_double2(pn.x + nn.x, pn.y + nn.y));
+  if (k >= 1 && k <= HN)
+    rows(F::SE + ((k - 1) >> 2), k - 1, make_double2(sk * pp.x - np.x, sk * pp.y - np.y),
+         make_double2(sk * pn.x - nn.x, sk * pn.y - nn.y));
+}
+
+// acc[i][j]: re and im of E, re and im of O of row tile i and column tile j.
+template <int N>
+__device__ __forceinline__ void fold_product(const d2* const (&A)[2], const double* const (&B)[JT],
+                                             d4 (&acc)[2][JT][4]) {
+  using F = Fold<N>;
+  d2 e[2], o[2];
+  double c[JT], n[JT];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    e[i] = A[i][0];
+    o[i] = A[i][F::SE * 64];
+#pragma unroll
+    for (int j = 0; j < JT; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[i][j][q] = d4{0.0, 0.0, 0.0, 0.0};
+  }
+#pragma unroll
+  for (int j = 0; j < JT; ++j) {
+    c[j] = B[j][0];
+    n[j] = B[j][F::SE * 64];
+  }
+#pragma unroll 2
+  for (int s = 0; s < F::SO; ++s) {
+    d2 e1[2], o1[2];
+    double c1[JT], n1[JT];
+    const int so = s + 1 < F::SO ? s + 1 : s;  // (there is one even step more)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      e1[i] = A[i][(s + 1) * 64];
+      o1[i] = A[i][(F::SE + so) * 64];
+    }
+#pragma unroll
+    for (int j = 0; j < JT; ++j) {
+      c1[j] = B[j][(s + 1) * 64];
+      n1[j] = B[j][(F::SE + so) * 64];
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < JT; ++j) {
+        acc[i][j][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(e[i][0], c[j], acc[i][j][0], 0, 0, 0);
+        acc[i][j][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(e[i][1], c[j], acc[i][j][1], 0, 0, 0);
+        acc[i][j][2] = __builtin_amdgcn_mfma_f64_16x16x4f64(o[i][0], n[j], acc[i][j][2], 0, 0, 0);
+        acc[i][j][3] = __builtin_amdgcn_mfma_f64_16x16x4f64(o[i][1], n[j], acc[i][j][3], 0, 0, 0);
+      }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      e[i] = e1[i];
+      o[i] = o1[i];
+    }
+#pragma unroll
+    for (int j = 0; j < JT; ++j) {
+      c[j] = c1[j];
+      n[j] = n1[j];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < JT; ++j) {
+      acc[i][j][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(e[i][0], c[j], acc[i][j][0], 0, 0, 0);
+      acc[i][j][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(e[i][1], c[j], acc[i][j][1], 0, 0, 0);
+    }
+}
+
+// Waves of a launch: pair, row group, column group, the last running fastest
+// (the waves of a workgroup share their rows).
+struct FoldWork {
+  int rows, cols, tiles;  // row groups of 2, column groups of JT; column tiles
+  int waves;              // of all pairs
+};
+
+template <int N>
+__device__ __forceinline__ int fold_columns(const RegArgs& a, const FoldWork& w, int cg, int lane,
+                                            const double* (&B)[JT]) {
+#pragma unroll
+  for (int j = 0; j < JT; ++j)
+    B[j] = (const double*)a.K + (size_t)min(cg * JT + j, w.tiles - 1) * Fold<N>::TILE + lane;
+  return min(JT, w.tiles - cg * JT);
+}
+
+template <int N>
+__global__ __launch_bounds__(256, 2) void k_reg_fold1(const RegArgs a, const FoldWork w) {
+  using F = Fold<N>;
+  const int q = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  if (q >= w.waves) return;
+  const int b = q / (w.rows * w.cols), rg = q / w.cols % w.rows, cg = q % w.cols;
+  const d2* A[2];
+  const double* B[JT];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) A[i] = fold_tile<N>(a, b, min(2 * rg + i, F::RT - 1)) + lane;
+  const int cols = fold_columns<N>(a, w, cg, lane, B);
+  d4 acc[2][JT][4];
+  fold_product<N>(A, B, acc);
+  d2* const T = (d2*)a.T + (size_t)b * 2 * w.tiles * F::TILE + lane;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int t = 2 * rg + i;
+    if (t >= F::RT) continue;
+#pragma unroll
+    for (int j = 0; j < JT; ++j) {
+      if (j >= cols) continue;
+      d2* const up = T + (size_t)(cg * JT + j) * F::TILE;
+      d2* const down = up + (size_t)w.tiles * F::TILE;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int step = 4 * t + r;  // of p; m starts at tile PT
+        if (t < F::PT && step >= F::SE) continue;
+        const int at = (t < F::PT ? step : F::SE + step - 4 * F::PT) * 64;
+        up[at] = d2{acc[i][j][0][r] - acc[i][j][3][r], acc[i][j][1][r] + acc[i][j][2][r]};
+        down[at] = d2{acc[i][j][0][r] + acc[i][j][3][r], acc[i][j][1][r] - acc[i][j][2][r]};
+      }
+    }
+  }
+}
+
+template <int N>
+__global__ __launch_bounds__(256, 2) void k_reg_fold2(const RegArgs a, const FoldWork w) {
+  using F = Fold<N>;
+  const int q = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  if (q >= w.waves) return;
+  const int per = w.rows * w.cols, b = q / per, rg = q / w.cols % w.rows, cg = q % w.cols;
+  const d2* A[2];
+  const double* B[JT];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) A[i] = (const d2*)a.T + ((size_t)b * 2 * w.tiles + 2 * rg + i) * F::TILE + lane;
+  const int cols = fold_columns<N>(a, w, cg, lane, B);
+  d4 acc[2][JT][4];
+  fold_product<N>(A, B, acc);
+  const int U = a.U, c = a.c;
+  double best = -1.0;
+  int bi = U * U;
+  const auto take = [&](bool in, int u, int v, double re, double im) __attribute__((always_inline)) {
+    const double m = re * re + im * im;
+    const int ii = u * U + v;
+    const bool win = in && (m > best || (m == best && ii < bi));
+    best = win ? m : best;
+    bi = win ? ii : bi;
+  };
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int t = 2 * rg + i;
+    const bool down = t >= w.tiles;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int wu = (down ? t - w.tiles : t) * 16 + 4 * r + (lane >> 4), u = down ? c - wu : c + wu;
+      const bool uin = wu <= c && u < U && !(down && wu == 0);
+#pragma unroll
+      for (int j = 0; j < JT; ++j) {
+        const int wv = (cg * JT + j) * 16 + (lane & 15);
+        const bool in = uin && j < cols && wv <= c;
+        const double er = acc[i][j][0][r], ei = acc[i][j][1][r], orr = acc[i][j][2][r], oi = acc[i][j][3][r];
+        take(in && c + wv < U, u, c + wv, er - oi, ei + orr);
+        take(in && wv > 0, u, c - wv, er + oi, ei - orr);
+      }
+    }
+  }
+  const ArgMax m = wave_argmax(best, (long long)bi);
+  if (lane == 0) {
+    a.tile_v[(size_t)b * per + rg * w.cols + cg] = m.v;
+    a.tile_i[(size_t)b * per + rg * w.cols + cg] = m.i;
+  }
+}
+
 __global__ __launch_bounds__(64) void k_reg_final(const RegArgs a, int tiles) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= a.B) return;
+  const int b = blockIdx.x;
   double v = -1.0;
   long long idx = (long long)a.U * a.U;
-  for (int t = 0; t < tiles; ++t) {
+  for (int t = threadIdx.x; t < tiles; t += 64) {
     const double m = a.tile_v[(size_t)b * tiles + t];
     const long long ii = a.tile_i[(size_t)b * tiles + t];
     if (better(m, ii, v, idx)) { v = m; idx = ii; }
   }
+  idx = wave_argmax(v, idx).i;
+  if (threadIdx.x) return;
   const int u = (int)(idx / a.U), w = (int)(idx % a.U);
   a.peak[4 * b + 2] = u;
   a.peak[4 * b + 3] = w;
@@ -388,25 +657,54 @@ int reg_window(int up, int* U, int* c) {
   return MRPIE_OK;
 }
 
+// The folded products need windows that fill their tiles of 16 + 16 samples.
+constexpr int kFoldMinU = 32;
+
 RegLayout reg_layout(int N, int B, int up) {
   RegLayout L{};
   int U, c;
   reg_window(up, &U, &c);
   const int chunk = std::max(1, std::min(B, kRegChunk));
-  const int t2 = 16 * gemm_rb(U);
-  const int tiles = ((U + t2 - 1) / t2) * ((U + t2 - 1) / t2);
+  const int t2 = U > 320 ? 64 : 32;  // (windows above 320 are always folded)
+  int tiles = ((U + t2 - 1) / t2) * ((U + t2 - 1) / t2);
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = ws_align(off + bytes); return o; };
-  L.chunk = chunk;
-  L.work = take((size_t)chunk * 2 * N * N * 16);
-  L.K = take((size_t)U * N * 16);
-  L.T = take((size_t)chunk * U * N * 16);
-  L.rowmax_v = take((size_t)chunk * N * 8);
-  L.rowmax_i = take((size_t)chunk * N * 8);
-  L.s0 = take((size_t)chunk * 2 * 4);
-  L.tile_v = take((size_t)chunk * tiles * 8);
-  L.tile_i = take((size_t)chunk * tiles * 8);
+  const auto place = [&](int n, size_t table, size_t t, size_t f) {
+    off = 0;
+    L.chunk = n;
+    L.work = take((size_t)n * 2 * N * N * 16);
+    L.K = take(table);
+    L.T = take((size_t)n * t);
+    L.rowmax_v = take((size_t)n * N * 8);
+    L.rowmax_i = take((size_t)n * N * 8);
+    L.s0 = take((size_t)n * 2 * 4);
+    L.tile_v = take((size_t)n * tiles * 8);
+    L.tile_i = take((size_t)n * tiles * 8);
+    L.F = take((size_t)n * f);
+  };
+  const size_t plain = (size_t)U * N * 16;
+  place(chunk, plain, plain, 0);
   L.total = off;
+  if (U < kFoldMinU) return L;
+  // The folded products lay out less for the table and more for each pair.
+  // They take no more memory than the plain ones: fewer pairs a pass if need
+  // be, down to half (few pairs of a small window stay with the plain GEMMs).
+  const int ct = c / 16 + 1, plain_tiles = tiles;
+  const size_t lanes = (size_t)(N / 4 + 1) * 64;            // Fold<N>::TILE
+  const size_t behind = (N / 16 + 1) - N * N / lanes;       // Fold<N>::RT - HOME
+  tiles = ct * ((ct + JT - 1) / JT);
+  L.fold = true;
+  int n = chunk;
+  do place(n, ct * lanes * 8, 2 * ct * lanes * 16, behind * lanes * 16);
+  while (off > L.total && --n);
+  if (2 * n < chunk || n == 0) {
+    tiles = plain_tiles;
+    L.fold = false;
+    place(chunk, plain, plain, 0);
+    return L;
+  }
+  const int passes = (B + n - 1) / n;  // of like size
+  place(std::max(1, (B + passes - 1) / passes), ct * lanes * 8, 2 * ct * lanes * 16, behind * lanes * 16);
   return L;
 }
 
@@ -422,6 +720,7 @@ static int register_impl(int B, const float2* ref, const float2* mov, int up, in
   a.norm = norm;
   a.work = (double2*)(ws + L.work);
   a.K = (double2*)(ws + L.K);
+  a.F = (double2*)(ws + L.F);
   a.T = (double2*)(ws + L.T);
   a.rowmax_v = (double*)(ws + L.rowmax_v);
   a.rowmax_i = (long long*)(ws + L.rowmax_i);
@@ -429,10 +728,9 @@ static int register_impl(int B, const float2* ref, const float2* mov, int up, in
   a.tile_v = (double*)(ws + L.tile_v);
   a.tile_i = (long long*)(ws + L.tile_i);
   MRPIE_HIP(ensure_lds((const void*)k_reg_cols<N>, reg_cols_lds(N)));
-  hipLaunchKernelGGL(k_reg_kmat, dim3(64), dim3(256), 0, s, a, N);
-  const int rb = gemm_rb(U), gt = (U + 16 * rb - 1) / (16 * rb);
-  const auto kg1 = rb == 4 ? k_reg_gemm1<N, 4> : k_reg_gemm1<N, 2>;
-  const auto kg2 = rb == 4 ? k_reg_gemm2<N, 4> : k_reg_gemm2<N, 2>;
+  const int gt = (U + 31) / 32, ct = c / 16 + 1;
+  if (L.fold) hipLaunchKernelGGL(k_reg_table<N>, dim3((ct * Fold<N>::TILE + 255) / 256), dim3(256), 0, s, a, ct);
+  else hipLaunchKernelGGL(k_reg_kmat, dim3(64), dim3(256), 0, s, a, N);
   for (int b0 = 0; b0 < B; b0 += L.chunk) {
     const int nb = std::min(L.chunk, B - b0);
     a.B = nb;
@@ -444,9 +742,22 @@ static int register_impl(int B, const float2* ref, const float2* mov, int up, in
     launch_k(TK_REG, k_reg_cols<N>, dim3(N / kRegCW, nb), dim3(256), reg_cols_lds(N), s, a);
     hipLaunchKernelGGL(k_reg_coarse<N>, dim3(N / kRegRW, nb), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_reg_s0, dim3(nb), dim3(256), 0, s, a, N);
-    launch_k(TK_GEMM, kg1, dim3((N + G1_TX - 1) / G1_TX, (U + 16 * rb - 1) / (16 * rb), nb), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(kg2, dim3(gt, gt, nb), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_reg_final, dim3((nb + 63) / 64), dim3(64), 0, s, a, gt * gt);
+    int tiles = gt * gt;
+    if (L.fold) {
+      constexpr int kSlots = 4 * Fold<N>::SE * 16 * Fold<N>::PT;
+      hipLaunchKernelGGL(k_reg_fold<N>, dim3((kSlots + 255) / 256, nb), dim3(256), 0, s, a);
+      FoldWork w{(Fold<N>::RT + 1) / 2, (ct + JT - 1) / JT, ct, 0};
+      w.waves = nb * w.rows * w.cols;
+      launch_k(TK_GEMM, k_reg_fold1<N>, dim3((w.waves + 3) / 4), dim3(256), 0, s, a, w);
+      w.rows = ct;
+      tiles = w.rows * w.cols;
+      w.waves = nb * tiles;
+      hipLaunchKernelGGL(k_reg_fold2<N>, dim3((w.waves + 3) / 4), dim3(256), 0, s, a, w);
+    } else {
+      launch_k(TK_GEMM, k_reg_gemm1<N>, dim3((N + G1_TX - 1) / G1_TX, gt, nb), dim3(256), 0, s, a);
+      hipLaunchKernelGGL(k_reg_gemm2<N>, dim3(gt, gt, nb), dim3(256), 0, s, a);
+    }
+    hipLaunchKernelGGL(k_reg_final, dim3(nb), dim3(64), 0, s, a, tiles);
   }
   MRPIE_HIP(hipGetLastError());
   return MRPIE_OK;

@@ -13,8 +13,9 @@ struct RegArgs {
   const float2* ref;   // [B][N][N]
   const float2* mov;   // [B][N][N]
   double2* work;       // [chunk][2][N][N]
-  double2* K;          // [U][N]
-  double2* T;          // [chunk][U][N]
+  double2* K;          // [U][N] (folded: the table)
+  double2* T;          // [chunk][U][N] (folded: row tiles)
+  double2* F;          // folded: the tiles of X that work has no room for
   double* rowmax_v;    // [chunk][N]
   long long* rowmax_i; // [chunk][N]
   int* s0;             // [chunk][2]
@@ -26,7 +27,8 @@ struct RegArgs {
 
 struct RegLayout {
   int chunk;
-  size_t work, K, T, rowmax_v, rowmax_i, s0, tile_v, tile_i, total;
+  bool fold;  // the products by symmetry
+  size_t work, K, T, rowmax_v, rowmax_i, s0, tile_v, tile_i, F, total;
 };
 
 RegLayout reg_layout(int N, int B, int up);

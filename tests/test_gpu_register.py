@@ -155,3 +155,21 @@ def test_register_across_pair_chunks(norm):
         if list(pk[b]) != list(po) or not np.allclose(sh[b], so, atol=1e-5):
             bad.append((b, pk[b].tolist(), po.tolist()))
     assert not bad, bad[:5]
+
+
+@pytest.mark.parametrize("N", [32, 64, 128, 192, 256])
+@pytest.mark.parametrize("up,B", [(20, 2), (21, 2), (22, 7), (43, 3), (63, 2), (64, 9), (85, 3), (213, 2), (214, 2),
+                                  (500, 1)])
+def test_register_folded_products_peaks_exact(N, up, B):
+    """Windows around the smallest that the folded products take (32 samples,
+    upsample 21), around whole tiles of 16 + 16 samples (upsample 43, 64, 85),
+    even and odd ones, with and without a full second column tile, and the
+    plain GEMMs' share; the Nyquist row and column carry power."""
+    rng = np.random.default_rng(1000 * N + up)
+    ref, mov, _ = pairs_shifted(rng, B, N, max_shift=N / 6.0)
+    for norm in (0, 1):
+        sh, pk = gpu_register(ref, mov, up, norm)
+        for b in range(B):
+            so, po = oracle.register64(ref[b].astype(np.complex128), mov[b].astype(np.complex128), up, norm)
+            assert list(pk[b]) == list(po), (norm, b, pk[b], po)
+            assert np.allclose(sh[b], so, atol=1e-5)
