@@ -362,13 +362,14 @@ __global__ __launch_bounds__(256) void k_reg_gemm2(const RegArgs a) {
 // columns) register r of tile t is step 4 t + r, lane by lane.
 //
 // A wave takes 2 row tiles x JT column tiles, 16 instructions of 64 cycles a
-// step for 8 operand loads, fetched one step ahead, so the matrix cores bound
-// it.  (2 x 4 tiles need more than 256 registers, and the compiler then moves
-// accumulators between the two register files at every instruction.)  32 pairs
-// of 256^2 at upsample 1000 (window 1500): fold + fold1 + fold2 20 + 192 + 766
-// us (50 TFLOP/s of fp64 in fold2) where the complex products took 616 +
-// 3530; 400 pairs at upsample 100 (window 150): 151 + 348 + 191 us, before
-// 950 + 607.
+// step for 8 operand loads, so the matrix cores bound it.  (2 x 4 tiles need
+// more than 256 registers, and the compiler then moves accumulators between
+// the two register files at every instruction.)  Operands are fetched two
+// steps ahead: one step, 1000 cycles, does not cover memory (fold1 of 200
+// pairs at upsample 100 174 against 141 us).  32 pairs of 256^2 at upsample
+// 1000 (window 1500): fold + fold1 + fold2 20 + 160 + 705 us (54 TFLOP/s of
+// fp64 in fold2) where the complex products took 616 + 3530; 400 pairs at
+// upsample 100 (window 150): 151 + 282 + 167 us, before 950 + 607.
 using d2 = double __attribute__((ext_vector_type(2)));
 using d4 = double __attribute__((ext_vector_type(4)));
 
@@ -449,63 +450,61 @@ template <int N>
 __device__ __forceinline__ void fold_product(const d2* const (&A)[2], const double* const (&B)[JT],
                                              d4 (&acc)[2][JT][4]) {
   using F = Fold<N>;
-  d2 e[2], o[2];
-  double c[JT], n[JT];
+  d2 e[3][2], o[3][2];          // steps s, s + 1, s + 2
+  double c[3][JT], n[3][JT];
+  const auto load = [&](int x, int s) __attribute__((always_inline)) {
+    const int se = min(s, F::SE - 1), so = min(s, F::SO - 1);  // (there is one even step more)
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    e[i] = A[i][0];
-    o[i] = A[i][F::SE * 64];
+    for (int i = 0; i < 2; ++i) {
+      e[x][i] = A[i][se * 64];
+      o[x][i] = A[i][(F::SE + so) * 64];
+    }
+#pragma unroll
+    for (int j = 0; j < JT; ++j) {
+      c[x][j] = B[j][se * 64];
+      n[x][j] = B[j][(F::SE + so) * 64];
+    }
+  };
+  load(0, 0);
+  load(1, 1);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < JT; ++j)
 #pragma unroll
       for (int q = 0; q < 4; ++q) acc[i][j][q] = d4{0.0, 0.0, 0.0, 0.0};
-  }
-#pragma unroll
-  for (int j = 0; j < JT; ++j) {
-    c[j] = B[j][0];
-    n[j] = B[j][F::SE * 64];
-  }
-#pragma unroll 2
+#pragma unroll 3
   for (int s = 0; s < F::SO; ++s) {
-    d2 e1[2], o1[2];
-    double c1[JT], n1[JT];
-    const int so = s + 1 < F::SO ? s + 1 : s;  // (there is one even step more)
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      e1[i] = A[i][(s + 1) * 64];
-      o1[i] = A[i][(F::SE + so) * 64];
-    }
-#pragma unroll
-    for (int j = 0; j < JT; ++j) {
-      c1[j] = B[j][(s + 1) * 64];
-      n1[j] = B[j][(F::SE + so) * 64];
-    }
+    load(2, s + 2);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < JT; ++j) {
-        acc[i][j][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(e[i][0], c[j], acc[i][j][0], 0, 0, 0);
-        acc[i][j][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(e[i][1], c[j], acc[i][j][1], 0, 0, 0);
-        acc[i][j][2] = __builtin_amdgcn_mfma_f64_16x16x4f64(o[i][0], n[j], acc[i][j][2], 0, 0, 0);
-        acc[i][j][3] = __builtin_amdgcn_mfma_f64_16x16x4f64(o[i][1], n[j], acc[i][j][3], 0, 0, 0);
+        acc[i][j][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(e[0][i][0], c[0][j], acc[i][j][0], 0, 0, 0);
+        acc[i][j][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(e[0][i][1], c[0][j], acc[i][j][1], 0, 0, 0);
+        acc[i][j][2] = __builtin_amdgcn_mfma_f64_16x16x4f64(o[0][i][0], n[0][j], acc[i][j][2], 0, 0, 0);
+        acc[i][j][3] = __builtin_amdgcn_mfma_f64_16x16x4f64(o[0][i][1], n[0][j], acc[i][j][3], 0, 0, 0);
       }
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      e[i] = e1[i];
-      o[i] = o1[i];
-    }
+    for (int x = 0; x < 2; ++x) {
 #pragma unroll
-    for (int j = 0; j < JT; ++j) {
-      c[j] = c1[j];
-      n[j] = n1[j];
+      for (int i = 0; i < 2; ++i) {
+        e[x][i] = e[x + 1][i];
+        o[x][i] = o[x + 1][i];
+      }
+#pragma unroll
+      for (int j = 0; j < JT; ++j) {
+        c[x][j] = c[x + 1][j];
+        n[x][j] = n[x + 1][j];
+      }
     }
   }
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < JT; ++j) {
-      acc[i][j][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(e[i][0], c[j], acc[i][j][0], 0, 0, 0);
-      acc[i][j][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(e[i][1], c[j], acc[i][j][1], 0, 0, 0);
+      acc[i][j][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(e[0][i][0], c[0][j], acc[i][j][0], 0, 0, 0);
+      acc[i][j][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(e[0][i][1], c[0][j], acc[i][j][1], 0, 0, 0);
     }
 }
 
