@@ -802,33 +802,50 @@ __global__ __launch_bounds__(256) void k_adj_p4(const AdjArgs a) {
 MRPIE_ADJ_KERNEL(k_adj_p5, adj_p5)
 
 // ---------------------------------------------------------------- reductions
-// loss += sum over the chunk's (position, column) partials, in order: each
-// of kLossBlocks workgroups sums one contiguous range, then one workgroup
-// adds the range sums
+// What is left of a chunk after its passes is one launch of independent
+// workgroups (k_adj_reduce: object tiles, probe, positions, loss ranges) and
+// one workgroup for the loss.  The first chunk sets the results and later
+// ones add to them, so nothing is cleared beforehand.  A loss + gradient call
+// of one chunk is 8 launches (15 with a launch for each of these and for each
+// clear): forward and backward of 25 positions of 32^2 x 3 in autograd 242 -> 209
+// us; 1600 positions of 256^2 x 3, 7 chunks, 6.40 -> 5.98 ms, where the small
+// reductions run beside the object tiles.
+
+// Sum of the chunk's (position, column) partials of the loss over one of
+// kLossBlocks contiguous ranges
 constexpr int kLossBlocks = 64;
-__global__ __launch_bounds__(256) void k_adj_loss_part(const AdjArgs a, int nb) {
-  __shared__ double red[16];
+__device__ __forceinline__ void adj_loss_part(const AdjArgs& a, int nb, int blk, double* red) {
   const int n = nb * a.N, per = (n + kLossBlocks - 1) / kLossBlocks;
-  const int i0 = blockIdx.x * per, i1 = min(n, i0 + per);
+  const int i0 = blk * per, i1 = min(n, i0 + per);
   double v = 0.0;
-  for (int i = i0 + threadIdx.x; i < i1; i += blockDim.x) v += a.loss_part[i];
+  for (int i = i0 + threadIdx.x; i < i1; i += 256) v += a.loss_part[i];
   v = block_sum(v, red);
-  if (threadIdx.x == 0) a.loss_blk[blockIdx.x] = v;
+  if (threadIdx.x == 0) a.loss_blk[blk] = v;
 }
 
-__global__ __launch_bounds__(64) void k_adj_loss(const AdjArgs a) {
+// loss (+)= the range sums in order, or, of up to kLossDirect partials (32
+// loads a thread, less than a launch costs), the partials themselves
+constexpr int kLossDirect = 8192;
+__global__ __launch_bounds__(256) void k_adj_loss(const AdjArgs a, int nb, double* out) {
   __shared__ double red[16];
-  double v = a.loss_blk[threadIdx.x];
+  const int n = nb * a.N;
+  double v = 0.0;
+  if (n <= kLossDirect) {
+    for (int i = threadIdx.x; i < n; i += 256) v += a.loss_part[i];
+  } else if (threadIdx.x < kLossBlocks) {
+    v = a.loss_blk[threadIdx.x];
+  }
   v = block_sum(v, red);
-  if (threadIdx.x == 0) *a.loss_acc += v;
+  if (threadIdx.x) return;
+  if (a.j0) v += *a.loss_acc;
+  *a.loss_acc = v;
+  if (out) *out = v;
 }
 
 // grad_pos[j] = sum over columns of the position partials
-__global__ __launch_bounds__(256) void k_adj_pos(const AdjArgs a, int nb) {
-  __shared__ double red[16];
-  const int b = blockIdx.x;
+__device__ __forceinline__ void adj_pos(const AdjArgs& a, int b, double* red) {
   double gy = 0.0, gx = 0.0;
-  for (int u = threadIdx.x; u < a.N; u += blockDim.x) {
+  for (int u = threadIdx.x; u < a.N; u += 256) {
     const double* pp = a.pos_part + ((size_t)b * a.N + u) * kPosSlots;
     gy += pp[0];
     gx += (pp[1] + pp[2]) + (pp[3] + pp[4]);
@@ -841,64 +858,78 @@ __global__ __launch_bounds__(256) void k_adj_pos(const AdjArgs a, int nb) {
   }
 }
 
-// grad_P += the chunk's group partials of 2 chi conj(o), in position order
-__global__ __launch_bounds__(256) void k_adj_probe(const AdjArgs a, int nb) {
+// grad_P (+)= the chunk's group partials of 2 chi conj(o), in position order
+__device__ __forceinline__ void adj_probe(const AdjArgs& a, int nb, int blk, int blocks) {
   const size_t MNN = (size_t)a.M * a.N * a.N;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < MNN; i += (size_t)gridDim.x * blockDim.x) {
-    float2 s = a.grad_probe[i];
+  for (size_t i = blk * (size_t)256 + threadIdx.x; i < MNN; i += (size_t)blocks * 256) {
+    float2 s = make_float2(0.f, 0.f);
+    if (a.j0) s = a.grad_probe[i];
     for (int b = 0; b < nb; b += kAdjGroup) s = cadd(s, a.Psi[(size_t)b * MNN + i]);
     a.grad_probe[i] = s;
   }
 }
 
-// grad_O += the chunk's S_{-f}(g) patches at their boxes, in position order.
+// grad_O (+)= the chunk's S_{-f}(g) patches at their boxes, in position order.
 // One workgroup per 16 x 16 object tile; it lists the overlapping boxes
-// first, so each pixel visits only those.
+// first (thread b tests box b), so each pixel visits only those.
 constexpr int kObjTile = 16;
-__global__ __launch_bounds__(256) void k_adj_object(const AdjArgs a, int nb) {
-  __shared__ int lst[kAdjChunk];
-  __shared__ int boxes[kAdjChunk][2];
-  __shared__ int cnt;
-  const int N = a.N;
-  const int ty0 = blockIdx.y * kObjTile, tx0 = blockIdx.x * kObjTile;
-  if (threadIdx.x == 0) cnt = 0;
+struct ObjLists {
+  int lst[kAdjChunk], box[kAdjChunk][2], cnt[4];
+};
+static_assert(kAdjChunk <= 256, "a thread per box");
+__device__ __forceinline__ void adj_object(const AdjArgs& a, int nb, int ty, int tx, ObjLists& s) {
+  const int N = a.N, ty0 = ty * kObjTile, tx0 = tx * kObjTile, b = threadIdx.x, wave = b >> 6;
+  const int j = a.j0 + min(b, nb - 1);
+  const int ny = box_corner(a.pos[2 * j], a.H - N, nullptr);
+  const int nx = box_corner(a.pos[2 * j + 1], a.W - N, nullptr);
+  const bool hit = b < nb && ny < ty0 + kObjTile && ny + N > ty0 && nx < tx0 + kObjTile && nx + N > tx0;
+  const unsigned long long mask = __ballot(hit);
+  s.cnt[wave] = __popcll(mask);
   __syncthreads();
-  for (int b = threadIdx.x; b < nb; b += blockDim.x) {
-    const int j = a.j0 + b;
-    const int ny = box_corner(a.pos[2 * j], a.H - N, nullptr);
-    const int nx = box_corner(a.pos[2 * j + 1], a.W - N, nullptr);
-    boxes[b][0] = ny;
-    boxes[b][1] = nx;
+  int at = __popcll(mask & ((1ull << (b & 63)) - 1)), n = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    if (w < wave) at += s.cnt[w];
+    n += s.cnt[w];
+  }
+  if (hit) {
+    s.lst[at] = b;
+    s.box[at][0] = ny;
+    s.box[at][1] = nx;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int n = 0;
-    for (int b = 0; b < nb; ++b) {
-      const int ny = boxes[b][0], nx = boxes[b][1];
-      if (ny < ty0 + kObjTile && ny + N > ty0 && nx < tx0 + kObjTile && nx + N > tx0) lst[n++] = b;
-    }
-    cnt = n;
-  }
-  __syncthreads();
-  const int y = ty0 + threadIdx.x / kObjTile, x = tx0 + threadIdx.x % kObjTile;
+  const int y = ty0 + b / kObjTile, x = tx0 + b % kObjTile;
   if (y >= a.H || x >= a.W) return;
-  float2 s = a.grad_obj[(size_t)y * a.W + x];
-  for (int q = 0; q < cnt; ++q) {
-    const int b = lst[q];
-    const int dy = y - boxes[b][0], dx = x - boxes[b][1];
-    if (dy >= 0 && dy < N && dx >= 0 && dx < N) s = cadd(s, a.G[chunk_off(b, N) + (size_t)dy * N + dx]);
+  float2 g = make_float2(0.f, 0.f);
+  if (a.j0) g = a.grad_obj[(size_t)y * a.W + x];
+  for (int q = 0; q < n; ++q) {
+    const int dy = y - s.box[q][0], dx = x - s.box[q][1];
+    if (dy >= 0 && dy < N && dx >= 0 && dx < N) g = cadd(g, a.G[chunk_off(s.lst[q], N) + (size_t)dy * N + dx]);
   }
-  a.grad_obj[(size_t)y * a.W + x] = s;
+  a.grad_obj[(size_t)y * a.W + x] = g;
 }
 
-__global__ void k_adj_zero(float2* p, size_t n, double* d) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-    p[i] = make_float2(0.f, 0.f);
-  if (d && blockIdx.x == 0 && threadIdx.x == 0) *d = 0.0;
-}
-
-__global__ void k_adj_loss_out(const double* acc, double* out) {
-  if (threadIdx.x == 0) *out = *acc;
+// Workgroups of a chunk's reductions: object tiles (the longest, first), probe
+// blocks, positions, loss ranges.
+struct ReduceGrid {
+  int tiles_x, tiles, probe, pos, loss;
+};
+__global__ __launch_bounds__(256) void k_adj_reduce(const AdjArgs a, int nb, const ReduceGrid g) {
+  __shared__ ObjLists lists;
+  __shared__ double red[16];
+  int k = blockIdx.x;
+  if (k < g.tiles) {
+    adj_object(a, nb, k / g.tiles_x, k % g.tiles_x, lists);
+    return;
+  }
+  k -= g.tiles;
+  if (k < g.probe) {
+    adj_probe(a, nb, k, g.probe);
+    return;
+  }
+  k -= g.probe;
+  if (k < g.pos) adj_pos(a, k, red);
+  else adj_loss_part(a, nb, k - g.pos, red);
 }
 
 // ---------------------------------------------------------------- host
@@ -939,11 +970,6 @@ int run_adjoint(const mrpie_problem* pb, int subpixel, const float2* obj, const 
   a.loss_blk = (double*)(w + L.loss_blk);
   a.loss_acc = (double*)(w + L.loss_acc);
   a.grad_obj = gobj; a.grad_probe = gprobe; a.grad_pos = gpos;
-  hipLaunchKernelGGL(k_adj_zero, dim3(1), dim3(64), 0, s, (float2*)nullptr, (size_t)0, a.loss_acc);
-  if (grads) {
-    hipLaunchKernelGGL(k_adj_zero, dim3(2048), dim3(256), 0, s, gobj, (size_t)pb->H * pb->W, (double*)nullptr);
-    hipLaunchKernelGGL(k_adj_zero, dim3(256), dim3(256), 0, s, gprobe, (size_t)M * N * N, (double*)nullptr);
-  }
   // LDS of the row passes (kAdjRowPos M transforms; P4 at least 2 kAdjRowPos)
   // at the padded pitch
   // col_pitch<N, 1, true>(), of the single-field column passes (kAdjCW1
@@ -973,18 +999,20 @@ int run_adjoint(const mrpie_problem* pb, int subpixel, const float2* obj, const 
     hipLaunchKernelGGL(k_adj_p1, gp1, blk, lp1, s, a);
     hipLaunchKernelGGL(k_adj_p2, dim3(N, (nb + kAdjRowPos - 1) / kAdjRowPos), blk, l2, s, a);
     launch_ku(TK_ADJ, nb, kp3, dim3(N / kAdjCWM, (nb + g3 - 1) / g3), blk, lcm, s, a);  // timed per position
-    hipLaunchKernelGGL(k_adj_loss_part, dim3(kLossBlocks), blk, 0, s, a, nb);
-    hipLaunchKernelGGL(k_adj_loss, dim3(1), dim3(kLossBlocks), 0, s, a);
+    ReduceGrid g{};
+    g.loss = nb * N > kLossDirect ? kLossBlocks : 0;
     if (grads) {
       hipLaunchKernelGGL(kp4, dim3(N, (nb + kAdjGroup - 1) / kAdjGroup), blk, l4, s, a);
       hipLaunchKernelGGL(k_adj_p5, g1, blk, lc1, s, a);
-      hipLaunchKernelGGL(k_adj_pos, dim3(nb), blk, 0, s, a, nb);
-      hipLaunchKernelGGL(k_adj_probe, dim3(512), blk, 0, s, a, nb);
-      hipLaunchKernelGGL(k_adj_object, dim3((pb->W + kObjTile - 1) / kObjTile, (pb->H + kObjTile - 1) / kObjTile),
-                         blk, 0, s, a, nb);
+      g.tiles_x = (pb->W + kObjTile - 1) / kObjTile;
+      g.tiles = g.tiles_x * ((pb->H + kObjTile - 1) / kObjTile);
+      g.probe = std::min(512, (M * N * N + 255) / 256);
+      g.pos = nb;
     }
+    const int blocks = g.tiles + g.probe + g.pos + g.loss;
+    if (blocks) hipLaunchKernelGGL(k_adj_reduce, dim3(blocks), blk, 0, s, a, nb, g);
+    hipLaunchKernelGGL(k_adj_loss, dim3(1), blk, 0, s, a, nb, j0 + nb == J ? loss_out : nullptr);
   }
-  if (loss_out) hipLaunchKernelGGL(k_adj_loss_out, dim3(1), dim3(64), 0, s, (const double*)a.loss_acc, loss_out);
   MRPIE_HIP(hipGetLastError());
   return MRPIE_OK;
 }
