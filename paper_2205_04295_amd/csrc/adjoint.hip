@@ -23,6 +23,7 @@
 #include <cmath>
 
 #include "adjoint.hpp"
+#include "wfft.hpp"
 
 namespace mrpie {
 
@@ -596,6 +597,163 @@ __device__ void adj_p4(const AdjArgs& a, float2* smem) {
   }
 }
 
+// P2 and P4 with the FFTs inside waves (wfft.hpp), for up to three modes of
+// 128 and 256 points: a wave takes G adjacent rows of a.group consecutive
+// positions, with nothing to wait for but its own loads (the workgroup-wide
+// stages above leave lanes idle in a row's butterflies and stop at two
+// barriers a stage).  Not for 192 points (12 of each array a lane), four
+// modes (P4 spills: 300 positions of 256^2 x 4 1478 against 1348 us), 64
+// points (1000 positions of 64^2 x 1 562 against 560 us, x 4 963 against 680:
+// 8 rows a wave are few waves) and few positions (8 of 256^2 x 3 and 32 of
+// 128^2 x 2 gain 0 to 3 %, fewer leave SIMDs without a wave).
+// 256 positions of 256^2 x 3: P2 187 -> 131 us, P4 251 -> 176 us.
+constexpr bool adj_wave_rows(int N, int M) { return (N == 128 || N == 256) && M <= 3; }
+// Groups of positions are halved until the launch has this many waves (the
+// card has 1024 SIMDs); a pass with fewer than kAdjFewWaves even then takes
+// the workgroups.
+constexpr int kAdjWaves = 1200, kAdjFewWaves = 1024;
+
+// This wave's rows and positions; false: none.
+template <int N>
+struct AdjRows {
+  using F = WaveFft<N>;
+  static constexpr int L = F::L, PT = F::PT, G = F::G, NU = N / G;
+  int b0, b1, l, row;
+  float2* sc;
+  __device__ __forceinline__ bool init(const AdjArgs& a, float2* smem) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int w = blockIdx.x * 4 + wave, grp = lane % G;
+    b0 = w / NU * a.group;
+    b1 = min(b0 + a.group, a.nb);
+    l = lane / G;
+    row = w % NU * G + grp;
+    sc = smem + wave * F::SCRATCH + grp * F::PLEN;
+    return b0 < a.nb;
+  }
+  // signed frequency of element i
+  __device__ __forceinline__ int freq(int i) const { return i < PT / 2 ? l + L * i : l + L * i - N; }
+};
+
+template <int N, int M>
+__device__ __forceinline__ void adj_p2_wave(const AdjArgs& a, float2* smem) {
+  using R = AdjRows<N>;
+  constexpr int L = R::L, PT = R::PT, ni = N == 128 ? 1 : 3;
+  constexpr size_t NN = (size_t)N * N;
+  R w;
+  if (!w.init(a, smem)) return;
+  const size_t at = (size_t)w.row * N + w.l;
+  WaveFft<N> f;
+  f.init(g_tw[ni], w.l);
+  float2 P[M][PT];
+#pragma unroll
+  for (int p = 0; p < M; ++p)
+#pragma unroll
+    for (int i = 0; i < PT; ++i) P[p][i] = a.probe[p * NN + at + L * i];
+  for (int b = w.b0; b < w.b1; ++b) {
+    float fy, fx;
+    frac_of(a, a.j0 + b, N, &fy, &fx);
+    float2 o[1][PT];
+    const float2* cp = a.Cp + chunk_off(b, N) + at;
+#pragma unroll
+    for (int i = 0; i < PT; ++i) o[0][i] = cp[L * i];
+    f.template run<1, false>(o, w.sc, w.l);
+#pragma unroll
+    for (int i = 0; i < PT; ++i)
+      o[0][i] = cscale(cmul(o[0][i], ramp(0, w.freq(i), 0.f, fx, 1.f, N)), 1.f / (float)N);
+    f.template run<1, true>(o, w.sc, w.l);
+    float2* ob = a.Ob + chunk_off(b, N) + at;
+    float2 v[M][PT];
+#pragma unroll
+    for (int i = 0; i < PT; ++i) {
+      ob[L * i] = o[0][i];
+#pragma unroll
+      for (int p = 0; p < M; ++p) v[p][i] = cmul(P[p][i], o[0][i]);
+    }
+    f.template run<M, false>(v, w.sc, w.l);
+    float2* psi = a.Psi + (size_t)b * M * NN + at;
+#pragma unroll
+    for (int p = 0; p < M; ++p)
+#pragma unroll
+      for (int i = 0; i < PT; ++i) psi[p * NN + L * i] = v[p][i];
+  }
+}
+
+template <int N, int M>
+__device__ __forceinline__ void adj_p4_wave(const AdjArgs& a, float2* smem) {
+  using R = AdjRows<N>;
+  constexpr int L = R::L, PT = R::PT, G = R::G, ni = N == 128 ? 1 : 3;
+  constexpr size_t NN = (size_t)N * N;
+  constexpr bool KEEP = M <= 2;  // the probe's rows stay in registers (more: in the caches)
+  R w;
+  if (!w.init(a, smem)) return;
+  const size_t at = (size_t)w.row * N + w.l;
+  const int lane = threadIdx.x & 63;
+  WaveFft<N> f;
+  f.init(g_tw[ni], w.l);
+  float2 P[KEEP ? M : 1][PT], acc[M][PT];
+#pragma unroll
+  for (int p = 0; p < M; ++p)
+#pragma unroll
+    for (int i = 0; i < PT; ++i) {
+      if constexpr (KEEP) P[p][i] = a.probe[p * NN + at + L * i];
+      acc[p][i] = make_float2(0.f, 0.f);
+    }
+  for (int b = w.b0; b < w.b1; ++b) {
+    float fy, fx;
+    frac_of(a, a.j0 + b, N, &fy, &fx);
+    float2 v[M][PT], go[2][PT];  // chi; g and o
+    const float2* psi = a.Psi + (size_t)b * M * NN + at;
+    const float2* ob = a.Ob + chunk_off(b, N) + at;
+#pragma unroll
+    for (int p = 0; p < M; ++p)
+#pragma unroll
+      for (int i = 0; i < PT; ++i) v[p][i] = psi[p * NN + L * i];
+#pragma unroll
+    for (int i = 0; i < PT; ++i) {
+      go[1][i] = ob[L * i];
+      go[0][i] = make_float2(0.f, 0.f);
+    }
+#pragma unroll
+    for (int p = 0; p < M; ++p) {
+      f.template run<1, true>(v + p, w.sc, w.l);
+#pragma unroll
+      for (int i = 0; i < PT; ++i) {
+        const float2 Pi = KEEP ? P[KEEP ? p : 0][i] : a.probe[p * NN + at + L * i];
+        acc[p][i] = cadd(acc[p][i], cscale(cmulc(v[p][i], go[1][i]), 2.f));  // 2 chi conj(o)
+        go[0][i] = cadd(go[0][i], cmulc(v[p][i], Pi));
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < PT; ++i) go[0][i] = cscale(go[0][i], 2.f);
+    f.template run<2, false>(go, w.sc, w.l);  // F_x g, F_x o
+    double gx = 0.0;
+#pragma unroll
+    for (int i = 0; i < PT; ++i) {
+      const int kx = w.freq(i);
+      // Re conj(F g) (i w) F o = -w Im(conj(F g) F o), w = 2 pi kx / N
+      const float2 cf = cmulc(go[1][i], go[0][i]);  // F o conj(F g)
+      gx += -2.0 * M_PI * (double)kx / (double)N * (double)cf.y / (double)N;
+      go[0][i] = cscale(cmul(go[0][i], ramp(0, kx, 0.f, fx, -1.f, N)), 1.f / (float)N);
+    }
+    f.template run<1, true>(go, w.sc, w.l);
+    float2* g = a.G + chunk_off(b, N) + at;
+#pragma unroll
+    for (int i = 0; i < PT; ++i) g[L * i] = go[0][i];
+    // the sum over all rows of the wave, in the first row's first slot of x
+    // (each row has four: lane / 4 is the row, lane % 4 the slot)
+    if (a.subpixel) {
+      gx = wave_sum(gx);
+      const int q = lane < 4 * G ? lane : 4 * G - 1;
+      a.pos_part[((size_t)b * N + (w.row - lane % G) + q / 4) * kPosSlots + 1 + q % 4] = q == 0 ? gx : 0.0;
+    }
+  }
+  float2* part = a.Psi + (size_t)w.b0 * M * NN + at;
+#pragma unroll
+  for (int p = 0; p < M; ++p)
+#pragma unroll
+    for (int i = 0; i < PT; ++i) part[p * NN + L * i] = acc[p][i];
+}
+
 // P5 (cols): the y part of the position gradient from F_y h and F_y C;
 // S_{-y}(h) = S_{-f}(g) -> G (the object-gradient term)
 template <int N>
@@ -801,6 +959,16 @@ __global__ __launch_bounds__(256) void k_adj_p4(const AdjArgs a) {
 }
 MRPIE_ADJ_KERNEL(k_adj_p5, adj_p5)
 
+#define MRPIE_ADJ_WAVES(NAME, FN)                                  \
+  template <int M>                                                 \
+  __global__ __launch_bounds__(256, 2) void NAME(const AdjArgs a) { \
+    extern __shared__ float2 smem[];                               \
+    if (a.N == 128) FN<128, M>(a, smem);                           \
+    else FN<256, M>(a, smem);                                      \
+  }
+MRPIE_ADJ_WAVES(k_adj_p2_wave, adj_p2_wave)
+MRPIE_ADJ_WAVES(k_adj_p4_wave, adj_p4_wave)
+
 // ---------------------------------------------------------------- reductions
 // What is left of a chunk after its passes is one launch of independent
 // workgroups (k_adj_reduce: object tiles, probe, positions, loss ranges) and
@@ -864,7 +1032,7 @@ __device__ __forceinline__ void adj_probe(const AdjArgs& a, int nb, int blk, int
   for (size_t i = blk * (size_t)256 + threadIdx.x; i < MNN; i += (size_t)blocks * 256) {
     float2 s = make_float2(0.f, 0.f);
     if (a.j0) s = a.grad_probe[i];
-    for (int b = 0; b < nb; b += kAdjGroup) s = cadd(s, a.Psi[(size_t)b * MNN + i]);
+    for (int b = 0; b < nb; b += a.group) s = cadd(s, a.Psi[(size_t)b * MNN + i]);
     a.grad_probe[i] = s;
   }
 }
@@ -984,6 +1152,10 @@ int run_adjoint(const mrpie_problem* pb, int subpixel, const float2* obj, const 
   const int cw1 = rd ? kAdjCWR : kAdjCW1;
   const size_t lp1 = rd ? (N + 2 * kAdjCWR * ((size_t)N + 16 / kAdjCWR)) * 8 : lc1;
   MRPIE_HIP(ensure_lds((const void*)k_adj_p1, lp1));
+  const auto kw2 = M == 1 ? k_adj_p2_wave<1> : M == 2 ? k_adj_p2_wave<2> : k_adj_p2_wave<3>;
+  const auto kw4 = M == 1 ? k_adj_p4_wave<1> : M == 2 ? k_adj_p4_wave<2> : k_adj_p4_wave<3>;
+  const int units = N == 256 ? AdjRows<256>::NU : AdjRows<128>::NU;
+  const size_t lw = 4 * 8 * (size_t)(N == 256 ? WaveFft<256>::SCRATCH : WaveFft<128>::SCRATCH);
   MRPIE_HIP(ensure_lds((const void*)k_adj_p2, l2));
   const auto kp4 = M <= 1 ? k_adj_p4<1> : M <= 2 ? k_adj_p4<2> : M <= 4 ? k_adj_p4<4> : k_adj_p4<MRPIE_MAX_MODES>;
   MRPIE_HIP(ensure_lds((const void*)kp4, l4));
@@ -997,12 +1169,19 @@ int run_adjoint(const mrpie_problem* pb, int subpixel, const float2* obj, const 
     a.nb = nb;
     const dim3 gp1(N / cw1, nb), g1(N / kAdjCW1, nb), blk(kAdjThreads);
     hipLaunchKernelGGL(k_adj_p1, gp1, blk, lp1, s, a);
-    hipLaunchKernelGGL(k_adj_p2, dim3(N, (nb + kAdjRowPos - 1) / kAdjRowPos), blk, l2, s, a);
+    const bool rw = adj_wave_rows(N, M) && units * nb >= kAdjFewWaves;
+    a.group = kAdjGroup;
+    if (rw)
+      while (a.group > 1 && units * ((nb + a.group - 1) / a.group) < kAdjWaves) a.group /= 2;
+    const dim3 gw((units * ((nb + a.group - 1) / a.group) + 3) / 4);
+    if (rw) hipLaunchKernelGGL(kw2, gw, blk, lw, s, a);
+    else hipLaunchKernelGGL(k_adj_p2, dim3(N, (nb + kAdjRowPos - 1) / kAdjRowPos), blk, l2, s, a);
     launch_ku(TK_ADJ, nb, kp3, dim3(N / kAdjCWM, (nb + g3 - 1) / g3), blk, lcm, s, a);  // timed per position
     ReduceGrid g{};
     g.loss = nb * N > kLossDirect ? kLossBlocks : 0;
     if (grads) {
-      hipLaunchKernelGGL(kp4, dim3(N, (nb + kAdjGroup - 1) / kAdjGroup), blk, l4, s, a);
+      if (rw) hipLaunchKernelGGL(kw4, gw, blk, lw, s, a);
+      else hipLaunchKernelGGL(kp4, dim3(N, (nb + kAdjGroup - 1) / kAdjGroup), blk, l4, s, a);
       hipLaunchKernelGGL(k_adj_p5, g1, blk, lc1, s, a);
       g.tiles_x = (pb->W + kObjTile - 1) / kObjTile;
       g.tiles = g.tiles_x * ((pb->H + kObjTile - 1) / kObjTile);

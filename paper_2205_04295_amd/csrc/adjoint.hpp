@@ -9,6 +9,7 @@ constexpr int kAdjChunk = 256;  // positions processed per pass
 constexpr int kPosSlots = 5;    // position-gradient partials per (position, row or column)
 
 struct AdjArgs {
+  int group;           // positions whose probe-gradient terms a partial sums
   int H, W, N, M, J, subpixel, j0, nb;  // nb: positions in the current chunk
   const float2* obj;
   const float2* probe;

@@ -128,3 +128,25 @@ def test_gradient_full_size_across_chunks():
     assert abs(L - Lo) <= 1e-5 * Lo
     assert rel_l2(gO, gOo) < 1e-4 and rel_l2(gP, gPo) < 1e-4
     assert rel_l2(gp, gpo) < 1e-3
+
+
+@pytest.mark.parametrize("N,M,J,subpixel", [(256, 3, 7, 1), (256, 3, 8, 1), (256, 3, 21, 1), (256, 1, 45, 0),
+                                            (256, 2, 75, 1), (128, 2, 31, 1), (128, 2, 33, 1), (128, 1, 77, 0),
+                                            (128, 3, 270, 1)])
+def test_gradient_row_waves(N, M, J, subpixel):
+    """The row passes with the FFTs inside waves, at the fewest positions that
+    they take (8 at 256^2, 32 at 128^2) and one fewer, with groups of 1, 2, 4
+    and 8 positions, the last group ragged, and a second chunk of 14 positions
+    that the workgroups take.  Tolerances as above."""
+    w = wl.small_case(320 + J, N + 40, N, M, J, subpixel=bool(subpixel), W=N + 33, name="gw")
+    O = w.O0.copy()
+    O[N // 2:, :] = w.O_true[N // 2:, :]
+    L, gO, gP, gp = gpu_grad(O, w.P0, w.pos0, w.I, subpixel)
+    Lo, gOo, gPo, gpo = oracle.loss_grad64(O.astype(complex), w.P0.astype(complex), w.pos0.astype(float),
+                                           w.I.astype(float), subpixel)
+    assert abs(L - Lo) <= 1e-5 * Lo
+    assert rel_l2(gO, gOo) < 1e-4 and rel_l2(gP, gPo) < 1e-4
+    if subpixel:
+        assert rel_l2(gp, gpo) < 1e-3
+    else:
+        assert np.all(gp == 0)
