@@ -102,7 +102,7 @@ def parse():
     ap.add_argument("--batch-large", type=int, default=32,
                     help="also measure a batch of this many jobs (0: skip)")
     ap.add_argument("--small", type=int, default=1,
-                    help="also time the 64^2 raster workload (LDS sweep vs row / column passes)")
+                    help="also time the 64^2 raster workload (persistent launch vs row / column passes)")
     ap.add_argument("--sparse-iters", type=int, default=20,
                     help="iterations of the sparse-scan study (half the positions; 0 = skip)")
     ap.add_argument("--calib", action="store_true",
@@ -677,7 +677,8 @@ def main():
                    "params": {k: v for k, v in w.params.items()}},
         "roofline": roof,
         "kernels_us": {k: round(v[0] * 1e3, 3) for k, v in kt.items()},
-        "kernels_us_sum_per_position": round(sum(v[0] for k, v in kt.items() if k in ("k_rows", "k_cols")) * 1e3, 3),
+        "kernels_us_sum_per_position": round(sum(v[0] / max(v[2], 1.0) for k, v in kt.items()
+                                                 if k in ("k_rows", "k_cols", "k_team")) * 1e3, 3),
         "us_per_position": round(ms_per_step * 1e3 / J, 3),
         "path_algorithmic_GBs": round(path_gbs, 1),
         "path_frac": round(path_gbs / HBM_PEAK_GBS, 4),
