@@ -297,6 +297,13 @@ int mrpie_fft2(int32_t N, int32_t B, void* data, int32_t inverse, void* stream);
  * is 0. */
 int mrpie_modulus(int32_t N, int32_t M, void* psi, const float* intens, void* stream);
 
+/* Test hook: mrpie_rpie_batched with every job in the persistent launch,
+ * whatever route that call would choose, and teams formed of at most
+ * `members` (1..32) workgroups of an XCD, as in a launch that finds the GPU
+ * busy.  Results equal those of full teams bitwise.  MRPIE_EUNSUPPORTED for
+ * probes that no team holds (256^2 x 7 or 8). */
+int mrpie_team_sweep(int32_t njobs, const mrpie_job* jobs, const mrpie_params* pr, int32_t members, void* stream);
+
 /* Subpixel registration of B pairs of N x N complex64 patches (Methods,
  * "Adam-based position refinement": 2-D phase correlation after
  * Guizar-Sicairos et al. 2008 with the matrix-multiply DFT evaluated only

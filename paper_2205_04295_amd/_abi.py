@@ -78,6 +78,7 @@ _SIGS = {
     "mrpie_rpie": (C.c_int, [C.POINTER(Problem), C.POINTER(Params), _P, _P, _P, _P, _P, _P, _P, _P, C.c_size_t, _P]),
     "mrpie_rpie_noalloc": (C.c_int, [C.POINTER(Problem), C.POINTER(Params), _P, _P, _P, _P, _P, _P, _P, _P]),
     "mrpie_rpie_batched": (C.c_int, [C.c_int32, C.c_void_p, C.POINTER(Params), C.POINTER(Tuning), _P]),
+    "mrpie_team_sweep": (C.c_int, [C.c_int32, C.c_void_p, C.POINTER(Params), C.c_int32, _P]),
     "mrpie_set_tuning": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.POINTER(Tuning)]),
     "mrpie_get_tuning": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.POINTER(Tuning)]),
     "mrpie_tuning_candidates": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.POINTER(Tuning), C.c_int32]),

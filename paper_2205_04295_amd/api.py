@@ -71,15 +71,8 @@ def rpie(obj, probe, pos, intens, adam=None, err=None, status=None, workspace=No
     return workspace
 
 
-def rpie_batched(jobs, stream=None, tuning=None, **params):
-    """Run independent M-rPIE reconstructions lock-step in shared launches.
-
-    jobs: list of dicts with GPU tensors obj, probe, pos, intens and optional
-    err, status, workspace.  Keyword arguments are the shared mrpie_params;
-    `tuning` (a dict of mrpie_tuning fields, optional) fixes the launch shape
-    of this call.  Returns the list of workspaces used."""
-    lib = _abi.load()
-    prm = make_params(**params)
+def _job_array(jobs, prm):
+    """(mrpie_job array, workspaces) of a list of job dicts."""
     arr = (_abi.Job * len(jobs))()
     keep = []
     for b, j in enumerate(jobs):
@@ -93,8 +86,31 @@ def rpie_batched(jobs, stream=None, tuning=None, **params):
                           _dev(j["pos"], torch.float32, "pos"), _dev(j["intens"], torch.float32, "intens"),
                           _opt(j.get("err"), torch.float32, "err"), _opt(j.get("status"), torch.int32, "status"),
                           _dev(ws, torch.uint8, "workspace"), C.c_size_t(ws.numel()))
+    return arr, keep
+
+
+def rpie_batched(jobs, stream=None, tuning=None, **params):
+    """Run independent M-rPIE reconstructions lock-step in shared launches.
+
+    jobs: list of dicts with GPU tensors obj, probe, pos, intens and optional
+    err, status, workspace.  Keyword arguments are the shared mrpie_params;
+    `tuning` (a dict of mrpie_tuning fields, optional) fixes the launch shape
+    of this call.  Returns the list of workspaces used."""
+    lib = _abi.load()
+    prm = make_params(**params)
+    arr, keep = _job_array(jobs, prm)
     tu = None if tuning is None else C.byref(_abi.Tuning(**tuning))
     check(lib.mrpie_rpie_batched(len(jobs), C.cast(arr, C.c_void_p), C.byref(prm), tu, _stream(stream)))
+    return keep
+
+
+def team_sweep(jobs, members=32, stream=None, **params):
+    """rpie_batched in the persistent launch whatever the route it would
+    choose, with teams of at most `members` workgroups (test hook)."""
+    lib = _abi.load()
+    prm = make_params(**params)
+    arr, keep = _job_array(jobs, prm)
+    check(lib.mrpie_team_sweep(len(jobs), C.cast(arr, C.c_void_p), C.byref(prm), members, _stream(stream)))
     return keep
 
 

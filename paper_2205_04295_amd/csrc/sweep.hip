@@ -1766,20 +1766,15 @@ int mrpie_get_tuning(int32_t N, int32_t M, int32_t batched, mrpie_tuning* t) {
   return MRPIE_OK;
 }
 
-int mrpie_rpie_batched(int32_t njobs, const mrpie_job* jobs, const mrpie_params* pr, const mrpie_tuning* tuning,
-                       void* stream) {
-  if (njobs < 0) return fail(MRPIE_EINVAL, "njobs=%d < 0", njobs);
-  if (tuning) {
-    int rc = check_tuning(tuning);
-    if (rc) return rc;
-  }
-  if (njobs == 0) return MRPIE_OK;
+// A batched call's jobs as records, after its checks.
+static int batch_records(int32_t njobs, const mrpie_job* jobs, const mrpie_params* pr, std::vector<JobRec>& recs,
+                         std::vector<float*>& errs) {
   if (!jobs || !pr) return fail(MRPIE_EINVAL, "null jobs or params");
   if (pr->subpixel || pr->refine || pr->propagator)
     return fail(MRPIE_EUNSUPPORTED, "batched sweeps take integer crops, no refinement and the far field "
                                     "(subpixel=%d refine=%d propagator=%d)", pr->subpixel, pr->refine, pr->propagator);
-  std::vector<JobRec> recs((size_t)njobs);
-  std::vector<float*> errs((size_t)njobs);
+  recs.resize((size_t)njobs);
+  errs.resize((size_t)njobs);
   for (int b = 0; b < njobs; ++b) {
     const mrpie_job& j = jobs[b];
     int rc = mrpie_validate(&j.problem, pr);
@@ -1792,6 +1787,21 @@ int mrpie_rpie_batched(int32_t njobs, const mrpie_job* jobs, const mrpie_params*
                      j.problem.H, j.problem.W, j.problem.N, j.problem.M, j.problem.J, pr->iterations};
     errs[b] = j.err_out;
   }
+  return MRPIE_OK;
+}
+
+int mrpie_rpie_batched(int32_t njobs, const mrpie_job* jobs, const mrpie_params* pr, const mrpie_tuning* tuning,
+                       void* stream) {
+  if (njobs < 0) return fail(MRPIE_EINVAL, "njobs=%d < 0", njobs);
+  if (tuning) {
+    int rc = check_tuning(tuning);
+    if (rc) return rc;
+  }
+  if (njobs == 0) return MRPIE_OK;
+  std::vector<JobRec> recs;
+  std::vector<float*> errs;
+  const int rc = batch_records(njobs, jobs, pr, recs, errs);
+  if (rc) return rc;
   if (pr->iterations == 0) return MRPIE_OK;
   Common c{pr->alpha_obj, pr->alpha_probe, pr->beta, pr->gamma, pr->iter_offset, pr->probe_update_start};
   Tuning tu{};
@@ -1799,6 +1809,21 @@ int mrpie_rpie_batched(int32_t njobs, const mrpie_job* jobs, const mrpie_params*
     tu = Tuning{tuning->rows_radix, tuning->cols_radix, tuning->rows_threads, tuning->lds_sweep, tuning->cols_width,
                 tuning->rows_inplace, tuning->rows_split};
   return run_sweep(c, recs.data(), njobs, errs.data(), (hipStream_t)stream, tuning ? &tu : nullptr);
+}
+
+int mrpie_team_sweep(int32_t njobs, const mrpie_job* jobs, const mrpie_params* pr, int32_t members, void* stream) {
+  if (njobs < 1) return fail(MRPIE_EINVAL, "njobs=%d < 1", njobs);
+  if (members < 1 || members > kTeamMembers) return fail(MRPIE_EINVAL, "members=%d not in [1, %d]", members, kTeamMembers);
+  std::vector<JobRec> recs;
+  std::vector<float*> errs;
+  const int rc = batch_records(njobs, jobs, pr, recs, errs);
+  if (rc) return rc;
+  for (int b = 0; b < njobs; ++b)
+    if (!team_fits(recs[b].N, recs[b].M))
+      return fail(MRPIE_EUNSUPPORTED, "job %d: no team holds %d modes of %d^2", b, recs[b].M, recs[b].N);
+  if (pr->iterations == 0) return MRPIE_OK;
+  Common c{pr->alpha_obj, pr->alpha_probe, pr->beta, pr->gamma, pr->iter_offset, pr->probe_update_start};
+  return run_team(c, recs.data(), njobs, errs.data(), (hipStream_t)stream, members);
 }
 
 }  // extern "C"

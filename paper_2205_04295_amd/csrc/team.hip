@@ -57,7 +57,7 @@ namespace {
 
 constexpr int kMaxWaves = 12;     // of a workgroup (template parameter WV: 8 or 12)
 constexpr int kMaxXcc = 16;       // values the XCC id register can take
-constexpr int kMaxSize = 32;      // members of a team
+constexpr int kMaxSize = kTeamMembers;  // members of a team
 // Jobs are of four classes by the members they need: teams of 32, 16, 8, 4.
 // The workgroups of an XCD take the jobs of class 0 as one team, then those
 // of class 1 as two teams, and so on.
@@ -97,6 +97,7 @@ static_assert(sizeof(TeamJob) <= 256 && kFlagOffset + kFlagWords * 4 <= 8192, "p
 struct TeamArgs {
   unsigned* ctrl;
   int expect;                    // workgroups of each XCD
+  int limit;                     // ... of which teams are formed at most
   int first[kClasses + 1];       // job[first[c] .. first[c + 1]) are class c's, longest first
   const TeamJob* job[kMaxTeamJobs];
 };
@@ -160,6 +161,38 @@ struct Glob {
     st<v2>(v2{v.x, v.y});
   }
 };
+
+// The arithmetic of a position, with its fused operations spelled out and no
+// others: run_units and run_loops compute the same bits, and left to itself
+// the compiler fuses a product into a sum or not by what stands around it
+// (the FFTs' sums are fused the same everywhere: nothing here fuses into them).
+#pragma clang fp contract(off)
+__device__ __forceinline__ float2 xmul(float2 a, float2 b) {  // a b
+  return mk(fmaf(a.x, b.x, -(a.y * b.y)), fmaf(a.x, b.y, a.y * b.x));
+}
+__device__ __forceinline__ float2 xmulc(float2 a, float2 b) {  // a conj(b)
+  return mk(fmaf(a.x, b.x, a.y * b.y), fmaf(a.y, b.x, -(a.x * b.y)));
+}
+__device__ __forceinline__ float2 xnmac(float2 v, float2 a, float2 b) {  // v - a b
+  return mk(fmaf(a.y, b.y, fmaf(-a.x, b.x, v.x)), fmaf(-a.y, b.x, fmaf(-a.x, b.y, v.y)));
+}
+__device__ __forceinline__ float2 xaxpy(float2 v, float2 a, float s) {  // v + s a
+  return mk(fmaf(a.x, s, v.x), fmaf(a.y, s, v.y));
+}
+__device__ __forceinline__ float2 xscale(float2 a, float s) { return mk(a.x * s, a.y * s); }
+__device__ __forceinline__ float xabs2(float2 a) { return fmaf(a.x, a.x, a.y * a.y); }
+__device__ __forceinline__ float xadd_abs2(float s, float2 a) { return fmaf(a.x, a.x, fmaf(a.y, a.y, s)); }
+__device__ __forceinline__ float xadd_dot(float s, float2 a, float2 b) {  // s + Re(a conj(b))
+  return s + fmaf(a.x, b.x, a.y * b.y);
+}
+__device__ __forceinline__ float xadd_cross(float s, float2 a, float2 b) {  // s + Im(a conj(b))
+  return s + fmaf(a.y, b.x, -(a.x * b.y));
+}
+// w top + (1 - w) v, the denominators of Eq. 5 and Eq. 6
+__device__ __forceinline__ float xblend(float w, float top, float v) { return fmaf(1.f - w, v, w * top); }
+// |Psi| - sqrt(I) at a pixel of power A, rs = 1 / sqrt(A), sq = sqrt(I)
+__device__ __forceinline__ float xmisfit(float A, float rs, float invN, float sq) { return fmaf(A * rs, invN, -sq); }
+#pragma clang fp contract(fast)
 
 // HW_REG_XCC_ID: the XCD this workgroup runs on
 __device__ __forceinline__ int xcc_id() { return __builtin_amdgcn_s_getreg((3 << 11) | 20) & (kMaxXcc - 1); }
@@ -517,7 +550,7 @@ __device__ __forceinline__ void run_units(const Common& cm, const JobRec& jb, fl
 #pragma unroll
       for (int k = 0; k < KM; ++k)
 #pragma unroll
-        for (int i = 0; i < PT; ++i) ps[i / 4][i % 4] += cabs2(Pr[k][i]);
+        for (int i = 0; i < PT; ++i) ps[i / 4][i % 4] = xadd_abs2(ps[i / 4][i % 4], Pr[k][i]);
     }
     mode_sums(std::false_type{}, ps, ps, ps, [&](auto gc, v4 sx, v4 sy, v4 sp) __attribute__((always_inline)) {
       constexpr int g = decltype(gc)::value;
@@ -559,7 +592,7 @@ __device__ __forceinline__ void run_units(const Common& cm, const JobRec& jb, fl
 #pragma unroll
         for (int k = 0; k < KM; ++k)
 #pragma unroll
-          for (int i = 0; i < PT; ++i) v[k][i] = cmul(Pr[k][i], o[i]);
+          for (int i = 0; i < PT; ++i) v[k][i] = xmul(Pr[k][i], o[i]);
         fft_modes(fwd, v, ln);
 #pragma unroll
         for (int k = 0; k < KM; ++k)
@@ -569,7 +602,7 @@ __device__ __forceinline__ void run_units(const Common& cm, const JobRec& jb, fl
           }
         if (mw == 0) {
 #pragma unroll
-          for (int i = 0; i < PT; ++i) m = fmaxf(m, cabs2(o[i]));
+          for (int i = 0; i < PT; ++i) m = fmaxf(m, xabs2(o[i]));
           m = wave_max(m);
         }
       }
@@ -617,11 +650,11 @@ __device__ __forceinline__ void run_units(const Common& cm, const JobRec& jb, fl
           }
           fft_modes(fwd, v, ln);
 #pragma unroll
-          for (int i = 0; i < PT; ++i) A[i] = cabs2(v[0][i]);
+          for (int i = 0; i < PT; ++i) A[i] = xabs2(v[0][i]);
 #pragma unroll
           for (int k = 1; k < KM; ++k)
 #pragma unroll
-            for (int i = 0; i < PT; ++i) A[i] += cabs2(v[k][i]);
+            for (int i = 0; i < PT; ++i) A[i] = xadd_abs2(A[i], v[k][i]);
           if (MW > 1) {
 #pragma unroll
             for (int g = 0; g < GR; ++g)
@@ -648,7 +681,7 @@ __device__ __forceinline__ void run_units(const Common& cm, const JobRec& jb, fl
             const float rs = A[i] > 0.f ? __builtin_amdgcn_rsqf(A[i]) : 0.f;
             const float sq = __builtin_amdgcn_sqrtf(Ic);
             if (mw == 0) {
-              const float d = A[i] * rs * invN - sq;
+              const float d = xmisfit(A[i], rs, invN, sq);
               e += (double)d * (double)d;
               isv += (double)Ic;
               bad |= !isfinite(A[i]);
@@ -658,7 +691,7 @@ __device__ __forceinline__ void run_units(const Common& cm, const JobRec& jb, fl
 #pragma unroll
           for (int k = 0; k < KM; ++k)
 #pragma unroll
-            for (int i = 0; i < PT; ++i) v[k][i] = cscale(v[k][i], A[i]);
+            for (int i = 0; i < PT; ++i) v[k][i] = xscale(v[k][i], A[i]);
           fft_modes(bwd, v, ln);
 #pragma unroll
           for (int k = 0; k < KM; ++k)
@@ -699,7 +732,7 @@ __device__ __forceinline__ void run_units(const Common& cm, const JobRec& jb, fl
           float gP[PT];
 #pragma unroll
           for (int i = 0; i < PT; ++i) {
-            const float dP = cm.beta * omax + (1.f - cm.beta) * cabs2(o[i]);
+            const float dP = xblend(cm.beta, omax, xabs2(o[i]));
             gP[i] = (upd_p && dP != 0.f) ? cm.alpha_probe / dP : 0.f;
           }
 #pragma unroll
@@ -709,12 +742,11 @@ __device__ __forceinline__ void run_units(const Common& cm, const JobRec& jb, fl
           for (int k = 0; k < KM; ++k)
 #pragma unroll
             for (int i = 0; i < PT; ++i) {
-              const float2 d = csub(v[k][i], cmul(Pr[k][i], o[i]));
-              const float2 t = cmulc(d, Pr[k][i]);
-              nx[i / 4][i % 4] += t.x;
-              ny[i / 4][i % 4] += t.y;
-              Pr[k][i] = cadd(Pr[k][i], cscale(cmulc(d, o[i]), gP[i]));
-              ps[i / 4][i % 4] += cabs2(Pr[k][i]);
+              const float2 d = xnmac(v[k][i], Pr[k][i], o[i]);
+              nx[i / 4][i % 4] = xadd_dot(nx[i / 4][i % 4], d, Pr[k][i]);
+              ny[i / 4][i % 4] = xadd_cross(ny[i / 4][i % 4], d, Pr[k][i]);
+              Pr[k][i] = xaxpy(Pr[k][i], xmulc(d, o[i]), gP[i]);
+              ps[i / 4][i % 4] = xadd_abs2(ps[i / 4][i % 4], Pr[k][i]);
             }
         }
         mode_sums(std::true_type{}, nx, ny, ps, [&](auto gc, v4 sx, v4 sy, v4 sp) __attribute__((always_inline)) {
@@ -724,9 +756,9 @@ __device__ __forceinline__ void run_units(const Common& cm, const JobRec& jb, fl
 #pragma unroll
           for (int x = 0; x < 4; ++x) {
             const int i = 4 * g + x;
-            const float dO = cm.gamma * pmaxv + (1.f - cm.gamma) * Ps[i];
+            const float dO = xblend(cm.gamma, pmaxv, Ps[i]);
             const float gO = dO != 0.f ? cm.alpha_obj / dO : 0.f;
-            const float2 on = cadd(o[i], cscale(mk(sx[x], sy[x]), gO));
+            const float2 on = xaxpy(o[i], mk(sx[x], sy[x]), gO);
             bad |= !(isfinite(on.x) && isfinite(on.y)) || !isfinite(sp[x]);
             ob.far(L * 8 * i).st2(on);
             Ps[i] = sp[x];
@@ -755,8 +787,8 @@ __device__ __forceinline__ void run_units(const Common& cm, const JobRec& jb, fl
 
 // ... by a team with fewer waves: every wave takes its units of a phase in
 // turn, mode by mode, with the probe, the sums and the error in memory.  Only
-// a launch that found the GPU busy gets here; sums are taken in run_units'
-// order.
+// a launch that found the GPU busy gets here (or one told to form small teams:
+// mrpie_team_sweep); sums are taken in run_units' order.
 template <int N, int KM, int WV>
 __device__ __forceinline__ void run_loops(const Common& cm, const JobRec& jb, float* err_out, int rank, int size,
                                           char* lds, Shared* sh) {
@@ -793,7 +825,7 @@ __device__ __forceinline__ void run_loops(const Common& cm, const JobRec& jb, fl
       for (int i = 0; i < PT; ++i) t[i] = 0.f;
       for (int p = q; p < M; p += MW)
 #pragma unroll
-        for (int i = 0; i < PT; ++i) t[i] += cabs2(probe(p, u * G + ln.grp, ln.l, i).ld2());
+        for (int i = 0; i < PT; ++i) t[i] = xadd_abs2(t[i], probe(p, u * G + ln.grp, ln.l, i).ld2());
 #pragma unroll
       for (int i = 0; i < PT; ++i) s[i] += t[i];
     }
@@ -823,12 +855,12 @@ __device__ __forceinline__ void run_loops(const Common& cm, const JobRec& jb, fl
 #pragma unroll
         for (int i = 0; i < PT; ++i) {
           o[i] = ob.far(L * 8 * i).ld2_team();
-          m = fmaxf(m, cabs2(o[i]));
+          m = fmaxf(m, xabs2(o[i]));
         }
         for (int p = 0; p < M; ++p) {
           float2 v[1][PT];
 #pragma unroll
-          for (int i = 0; i < PT; ++i) v[0][i] = cmul(probe(p, r, l, i).ld2(), o[i]);
+          for (int i = 0; i < PT; ++i) v[0][i] = xmul(probe(p, r, l, i).ld2(), o[i]);
           f.template run<1, false>(v, ln.sc, (int)l);
 #pragma unroll
           for (int i = 0; i < PT; ++i) ex(p, r, l + L * i).st2(v[0][i]);
@@ -854,7 +886,7 @@ __device__ __forceinline__ void run_loops(const Common& cm, const JobRec& jb, fl
             f.template run<1, false>(v, ln.sc, (int)l);
 #pragma unroll
             for (int i = 0; i < PT; ++i) {
-              t[i] += cabs2(v[0][i]);
+              t[i] = xadd_abs2(t[i], v[0][i]);
               ex(p, l + L * i, c).st2(v[0][i]);
             }
           }
@@ -869,7 +901,7 @@ __device__ __forceinline__ void run_loops(const Common& cm, const JobRec& jb, fl
           const float Ic = fmaxf(g.far(L * N * 4 * i).template ld<float>(), 0.f);
           const float rs = A[i] > 0.f ? __builtin_amdgcn_rsqf(A[i]) : 0.f;
           const float sq = __builtin_amdgcn_sqrtf(Ic);
-          const float d = A[i] * rs * invN - sq;
+          const float d = xmisfit(A[i], rs, invN, sq);
           e += (double)d * (double)d;
           isv += (double)Ic;
           bad |= !isfinite(A[i]);
@@ -887,7 +919,7 @@ __device__ __forceinline__ void run_loops(const Common& cm, const JobRec& jb, fl
         for (int p = 0; p < M; ++p) {
           float2 v[1][PT];
 #pragma unroll
-          for (int i = 0; i < PT; ++i) v[0][i] = cscale(ex(p, l + L * i, c).ld2_team(), A[i]);
+          for (int i = 0; i < PT; ++i) v[0][i] = xscale(ex(p, l + L * i, c).ld2_team(), A[i]);
           f.template run<1, true>(v, ln.sc, (int)l);
 #pragma unroll
           for (int i = 0; i < PT; ++i) ex(p, l + L * i, c).st2(v[0][i]);
@@ -905,7 +937,7 @@ __device__ __forceinline__ void run_loops(const Common& cm, const JobRec& jb, fl
 #pragma unroll
         for (int i = 0; i < PT; ++i) {
           o[i] = ob.far(L * 8 * i).ld2_team();
-          const float dP = cm.beta * omax + (1.f - cm.beta) * cabs2(o[i]);
+          const float dP = xblend(cm.beta, omax, xabs2(o[i]));
           gP[i] = (upd_p && dP != 0.f) ? cm.alpha_probe / dP : 0.f;
           num[i] = mk(0.f, 0.f);
           Ps[i] = ps[i] = 0.f;
@@ -926,11 +958,11 @@ __device__ __forceinline__ void run_loops(const Common& cm, const JobRec& jb, fl
 #pragma unroll
             for (int i = 0; i < PT; ++i) {
               float2 P = probe(p, r, l, i).ld2();
-              tP[i] += cabs2(P);
-              const float2 d = csub(v[0][i], cmul(P, o[i]));
-              tn[i] = cadd(tn[i], cmulc(d, P));
-              P = cadd(P, cscale(cmulc(d, o[i]), gP[i]));
-              tp[i] += cabs2(P);
+              tP[i] = xadd_abs2(tP[i], P);
+              const float2 d = xnmac(v[0][i], P, o[i]);
+              tn[i] = mk(xadd_dot(tn[i].x, d, P), xadd_cross(tn[i].y, d, P));
+              P = xaxpy(P, xmulc(d, o[i]), gP[i]);
+              tp[i] = xadd_abs2(tp[i], P);
               probe(p, r, l, i).st2(P);
             }
           }
@@ -943,9 +975,9 @@ __device__ __forceinline__ void run_loops(const Common& cm, const JobRec& jb, fl
         }
 #pragma unroll
         for (int i = 0; i < PT; ++i) {
-          const float dO = cm.gamma * pmaxv + (1.f - cm.gamma) * Ps[i];
+          const float dO = xblend(cm.gamma, pmaxv, Ps[i]);
           const float gO = dO != 0.f ? cm.alpha_obj / dO : 0.f;
-          const float2 on = cadd(o[i], cscale(num[i], gO));
+          const float2 on = xaxpy(o[i], num[i], gO);
           bad |= !(isfinite(on.x) && isfinite(on.y)) || !isfinite(ps[i]);
           ob.far(L * 8 * i).st2(on);
           m = fmaxf(m, ps[i]);
@@ -1056,7 +1088,7 @@ __global__ __launch_bounds__(WV * 64, WV / 4) void k_team(const TeamArgs a) {
       n &= ~kClosed;
     }
     sh.rank = (int)t;
-    sh.size = (t & kClosed) ? 0 : (int)n;
+    sh.size = (t & kClosed) ? 0 : min((int)n, a.limit);
   }
   __syncthreads();
   const int me = __builtin_amdgcn_readfirstlane(sh.rank), there = __builtin_amdgcn_readfirstlane(sh.size);
@@ -1194,10 +1226,10 @@ bool team_suits(int N, int M, int njobs) {
 
 bool team_fits(int N, int M) { return job_km(N, M, N == 256 && M == 3 ? 12 : 8, kMaxSize) > 0; }
 
-int run_team(const Common& c, const JobRec* jobs, int njobs, float* const* err_out, hipStream_t s) {
+int run_team(const Common& c, const JobRec* jobs, int njobs, float* const* err_out, hipStream_t s, int limit) {
   if (njobs > kMaxTeamJobs) {
     for (int b = 0; b < njobs; b += kMaxTeamJobs) {
-      const int rc = run_team(c, jobs + b, std::min(kMaxTeamJobs, njobs - b), err_out ? err_out + b : nullptr, s);
+      const int rc = run_team(c, jobs + b, std::min(kMaxTeamJobs, njobs - b), err_out ? err_out + b : nullptr, s, limit);
       if (rc) return rc;
     }
     return MRPIE_OK;
@@ -1229,7 +1261,7 @@ int run_team(const Common& c, const JobRec* jobs, int njobs, float* const* err_o
         part[n].T = std::min(most, jobs[b].T - it);
         err[n++] = err_out && err_out[b] ? err_out[b] + it : nullptr;
       }
-      const int rc = run_team(ci, part.data(), n, err.data(), s);
+      const int rc = run_team(ci, part.data(), n, err.data(), s, limit);
       if (rc) return rc;
     }
     return MRPIE_OK;
@@ -1268,6 +1300,7 @@ int run_team(const Common& c, const JobRec* jobs, int njobs, float* const* err_o
   for (int k = 1; k <= kClasses; ++k) a.first[k] = std::max(a.first[k], a.first[k - 1]);
   // a call with a team for every job needs no more workgroups than those
   a.expect = njobs <= nxcc ? kMaxSize >> *std::min_element(cls.begin(), cls.end()) : kMaxSize;
+  a.limit = limit;
   const TeamLaunch tl = team_kernel(N, waves);
   MRPIE_HIP(ensure_lds((const void*)tl.k, tl.lds));
   int rc = launch_init_twiddles(s);

@@ -30,22 +30,27 @@ __device__ __forceinline__ void wave_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// 12 points as 3 x 4, natural order in and out.  Its fused operations and
+// those of the 192-point twiddles are spelled out: chosen by the compiler they
+// differ between one transform and two side by side, and the sweep's results
+// must not depend on which of the two a wave runs.
+#pragma clang fp contract(off)
 template <bool INV>
 __device__ __forceinline__ float2 cmulw(float2 a, float c, float s) {  // a * (c -+ i s)
-  return INV ? mk(a.x * c - a.y * s, a.y * c + a.x * s) : mk(a.x * c + a.y * s, a.y * c - a.x * s);
+  return INV ? mk(fmaf(a.x, c, -(a.y * s)), fmaf(a.y, c, a.x * s)) : mk(fmaf(a.x, c, a.y * s), fmaf(a.y, c, -(a.x * s)));
 }
-
-// 12 points as 3 x 4, natural order in and out
 template <bool INV>
 __device__ __forceinline__ void dft12(float2* v) {
   constexpr float c1 = 0.86602540378443864676f, h = 0.5f;
   float2 t[3][4];
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
-    float2 u[3] = {v[a], v[a + 4], v[a + 8]};
-    dft3<INV>(u);
-#pragma unroll
-    for (int b = 0; b < 3; ++b) t[b][a] = u[b];
+    const float2 t1 = cadd(v[a + 4], v[a + 8]), t2 = csub(v[a + 4], v[a + 8]);
+    const float2 m = mk(fmaf(-h, t1.x, v[a].x), fmaf(-h, t1.y, v[a].y));
+    constexpr float s = INV ? c1 : -c1;
+    t[0][a] = cadd(v[a], t1);
+    t[1][a] = mk(fmaf(-s, t2.y, m.x), fmaf(s, t2.x, m.y));
+    t[2][a] = mk(fmaf(s, t2.y, m.x), fmaf(-s, t2.x, m.y));
   }
   t[1][1] = cmulw<INV>(t[1][1], c1, h);
   t[1][2] = cmulw<INV>(t[1][2], h, c1);
@@ -60,6 +65,7 @@ __device__ __forceinline__ void dft12(float2* v) {
     for (int c = 0; c < 4; ++c) v[b + 3 * c] = t[b][c];
   }
 }
+#pragma clang fp contract(fast)
 
 // one pad element every eight spreads the stages' strided accesses over the
 // LDS banks (first-stage writes of lane l start at 9 l)
@@ -116,7 +122,8 @@ struct WaveFft {
 
   template <bool INV>
   __device__ __forceinline__ static float2 tmul(float2 a, float2 w) {
-    return INV ? cmulc(a, w) : cmul(a, w);
+    if constexpr (N == 192) return cmulw<INV>(a, w.x, -w.y);  // w = c - i s
+    else return INV ? cmulc(a, w) : cmul(a, w);
   }
 
   // A stage's exchange: outputs to the scratch, inputs of the next from it.

@@ -1,0 +1,64 @@
+"""Persistent sweep in teams with too few workgroups for their job's units (what
+a launch forms when it finds the GPU busy): every wave takes its units in
+turn.  Sums are taken in the full teams' order, so the results are theirs bit
+for bit; the oracle's to the sweep's tolerance (rel L2 1e-4, M-ePIE weights as
+in the tests of full teams)."""
+import numpy as np
+import pytest
+import torch
+
+from synth import workloads as wl
+
+from gpu_util import need_gpu, rel_l2, run_oracle, to_dev
+
+pytestmark = pytest.mark.gpu
+
+EPIE = dict(alpha_obj=0.9, alpha_probe=0.9, beta=1.0, gamma=1.0)
+
+
+@pytest.fixture(autouse=True)
+def _gpu():
+    need_gpu()
+
+
+def team(ws, members, **prm):
+    from paper_2205_04295_amd import api
+    devs = [to_dev(w) for w in ws]
+    jobs = [dict(obj=d["obj"], probe=d["probe"], pos=d["pos"], intens=d["I"],
+                 err=torch.zeros(prm["iterations"], dtype=torch.float32, device="cuda:0"),
+                 status=torch.zeros(1, dtype=torch.int32, device="cuda:0")) for d in devs]
+    api.team_sweep(jobs, members=members, **prm)
+    torch.cuda.synchronize()
+    return [dict(O=j["obj"].cpu().numpy(), P=j["probe"].cpu().numpy(), err=j["err"].cpu().numpy(),
+                 status=int(j["status"].item())) for j in jobs]
+
+
+def check(ws, members, prm):
+    for weights in (dict(beta=0.6, gamma=0.3), dict()):
+        full = team(ws, 32, **dict(prm, **weights))
+        got = team(ws, members, **dict(prm, **weights))
+        for a, b in zip(got, full):
+            assert np.array_equal(a["O"], b["O"]) and np.array_equal(a["P"], b["P"])
+            assert np.array_equal(a["err"], b["err"]) and a["status"] == b["status"]
+    o = run_oracle(ws[0], prm)
+    assert rel_l2(got[0]["O"], o["O"]) < 1e-4
+    assert rel_l2(got[0]["P"], o["P"]) < 1e-4
+
+
+# a team of one, odd sizes, one member short; mode counts that leave some
+# waves a mode less (5 of 192^2 in twos, 5 of 256^2 in threes); several jobs a team
+@pytest.mark.parametrize("N,M,jobs,J,members", [
+    (32, 8, 1, 5, 1), (32, 3, 33, 3, 1), (64, 1, 1, 4, 3), (64, 5, 1, 4, 3), (64, 7, 33, 3, 3), (128, 2, 1, 3, 1),
+    (128, 3, 9, 3, 10), (128, 7, 17, 2, 10), (192, 1, 2, 3, 10), (192, 5, 1, 3, 10), (256, 1, 1, 3, 10),
+    (256, 3, 1, 3, 31), (256, 3, 9, 3, 10), (256, 4, 1, 2, 3), (256, 5, 1, 2, 10), (256, 3, 1, 2, 1)])
+def test_small_teams_match_full_ones(N, M, jobs, J, members):
+    ws = [wl.small_case(800 + b % 2, N + 19, N, M, J, W=N + 26, name=f"s{b % 2}") for b in range(jobs)]
+    check(ws, members, dict(EPIE, iterations=2))
+
+
+@pytest.mark.parametrize("members", [1, 3, 10])
+def test_small_teams_of_mixed_sizes(members):
+    specs = [(128, 3), (64, 2), (256, 3), (192, 3), (32, 5), (256, 1), (64, 8), (128, 5), (192, 2), (32, 1)]
+    ws = [wl.small_case(820 + i, N + 21, N, M, 3 + i % 2, W=N + 12, name=f"x{i}") for i, (N, M) in enumerate(specs)]
+    ws[3].pos0[1] = (999.0, -4.0)  # clamped and flagged in both
+    check(ws, members, dict(EPIE, iterations=2, probe_update_start=1))
