@@ -55,6 +55,8 @@ extern "C" {
 #define MRPIE_STATUS_NONFINITE 1   /* a NaN/Inf reached the object, probe or error */
 #define MRPIE_STATUS_POS_CLAMPED 2 /* a box corner was outside [0,H-N]x[0,W-N]
                                       (or not finite) and was clamped */
+#define MRPIE_STATUS_UNFINISHED 4  /* a persistent sweep waited in vain (20 s) for one of its
+                                      workgroups and left: the job is not, or only partly, swept */
 
 #define MRPIE_MAX_MODES 8
 
@@ -300,9 +302,13 @@ int mrpie_modulus(int32_t N, int32_t M, void* psi, const float* intens, void* st
 /* Test hook: mrpie_rpie_batched with every job in the persistent launch,
  * whatever route that call would choose, and teams formed of at most
  * `members` (1..32) workgroups of an XCD, as in a launch that finds the GPU
- * busy.  Results equal those of full teams bitwise.  MRPIE_EUNSUPPORTED for
- * probes that no team holds (256^2 x 7 or 8). */
-int mrpie_team_sweep(int32_t njobs, const mrpie_job* jobs, const mrpie_params* pr, int32_t members, void* stream);
+ * busy.  Results equal those of full teams bitwise.  wait_ns > 0
+ * lets a workgroup's wait for its team give up after that many nanoseconds
+ * instead of 20 s; jobs that end so, or are not begun, are
+ * flagged MRPIE_STATUS_UNFINISHED.  MRPIE_EUNSUPPORTED for probes that no team
+ * holds (256^2 x 7 or 8). */
+int mrpie_team_sweep(int32_t njobs, const mrpie_job* jobs, const mrpie_params* pr, int32_t members, int32_t wait_ns,
+                     void* stream);
 
 /* Subpixel registration of B pairs of N x N complex64 patches (Methods,
  * "Adam-based position refinement": 2-D phase correlation after

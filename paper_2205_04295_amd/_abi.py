@@ -19,6 +19,7 @@ MRPIE_EWORKSPACE = -4
 NOALLOC_MAX_BYTES = 16 << 20
 STATUS_NONFINITE = 1
 STATUS_POS_CLAMPED = 2
+STATUS_UNFINISHED = 4
 
 
 class Problem(C.Structure):
@@ -78,7 +79,7 @@ _SIGS = {
     "mrpie_rpie": (C.c_int, [C.POINTER(Problem), C.POINTER(Params), _P, _P, _P, _P, _P, _P, _P, _P, C.c_size_t, _P]),
     "mrpie_rpie_noalloc": (C.c_int, [C.POINTER(Problem), C.POINTER(Params), _P, _P, _P, _P, _P, _P, _P, _P]),
     "mrpie_rpie_batched": (C.c_int, [C.c_int32, C.c_void_p, C.POINTER(Params), C.POINTER(Tuning), _P]),
-    "mrpie_team_sweep": (C.c_int, [C.c_int32, C.c_void_p, C.POINTER(Params), C.c_int32, _P]),
+    "mrpie_team_sweep": (C.c_int, [C.c_int32, C.c_void_p, C.POINTER(Params), C.c_int32, C.c_int32, _P]),
     "mrpie_set_tuning": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.POINTER(Tuning)]),
     "mrpie_get_tuning": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.POINTER(Tuning)]),
     "mrpie_tuning_candidates": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.POINTER(Tuning), C.c_int32]),

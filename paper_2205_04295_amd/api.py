@@ -104,13 +104,15 @@ def rpie_batched(jobs, stream=None, tuning=None, **params):
     return keep
 
 
-def team_sweep(jobs, members=32, stream=None, **params):
+def team_sweep(jobs, members=32, wait_ns=0, stream=None, **params):
     """rpie_batched in the persistent launch whatever the route it would
-    choose, with teams of at most `members` workgroups (test hook)."""
+    choose, with teams of at most `members` workgroups whose waits give up
+    after `wait_ns` nanoseconds (0: 20 s) (test hook)."""
     lib = _abi.load()
     prm = make_params(**params)
     arr, keep = _job_array(jobs, prm)
-    check(lib.mrpie_team_sweep(len(jobs), C.cast(arr, C.c_void_p), C.byref(prm), members, _stream(stream)))
+    check(lib.mrpie_team_sweep(len(jobs), C.cast(arr, C.c_void_p), C.byref(prm), members, wait_ns,
+                               _stream(stream)))
     return keep
 
 

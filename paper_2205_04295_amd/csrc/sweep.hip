@@ -1811,8 +1811,10 @@ int mrpie_rpie_batched(int32_t njobs, const mrpie_job* jobs, const mrpie_params*
   return run_sweep(c, recs.data(), njobs, errs.data(), (hipStream_t)stream, tuning ? &tu : nullptr);
 }
 
-int mrpie_team_sweep(int32_t njobs, const mrpie_job* jobs, const mrpie_params* pr, int32_t members, void* stream) {
+int mrpie_team_sweep(int32_t njobs, const mrpie_job* jobs, const mrpie_params* pr, int32_t members, int32_t wait_ns,
+                     void* stream) {
   if (njobs < 1) return fail(MRPIE_EINVAL, "njobs=%d < 1", njobs);
+  if (wait_ns < 0) return fail(MRPIE_EINVAL, "wait_ns=%d < 0", wait_ns);
   if (members < 1 || members > kTeamMembers) return fail(MRPIE_EINVAL, "members=%d not in [1, %d]", members, kTeamMembers);
   std::vector<JobRec> recs;
   std::vector<float*> errs;
@@ -1823,7 +1825,7 @@ int mrpie_team_sweep(int32_t njobs, const mrpie_job* jobs, const mrpie_params* p
       return fail(MRPIE_EUNSUPPORTED, "job %d: no team holds %d modes of %d^2", b, recs[b].M, recs[b].N);
   if (pr->iterations == 0) return MRPIE_OK;
   Common c{pr->alpha_obj, pr->alpha_probe, pr->beta, pr->gamma, pr->iter_offset, pr->probe_update_start};
-  return run_team(c, recs.data(), njobs, errs.data(), (hipStream_t)stream, members);
+  return run_team(c, recs.data(), njobs, errs.data(), (hipStream_t)stream, members, wait_ns);
 }
 
 }  // extern "C"

@@ -121,12 +121,13 @@ void launch_finish(const LaunchArgs& a, int nb, float* const* err_out, hipStream
 // workgroups, one XCD each, run a job from its first position to its last.
 // team_fits: whether a team can hold a job of M modes of N^2; team_suits:
 // whether it is also the faster way in a call of `njobs` such jobs.  `limit`:
-// workgroups of an XCD that teams are formed of at most.
+// workgroups of an XCD that teams are formed of at most; `wait_ns`: when a
+// wait inside a job gives up (0: after 20 s).
 constexpr int kTeamMembers = 32;
 bool team_fits(int N, int M);
 bool team_suits(int N, int M, int njobs);
 int run_team(const Common& c, const JobRec* jobs, int njobs, float* const* err_out, hipStream_t s,
-             int limit = kTeamMembers);
+             int limit = kTeamMembers, int wait_ns = 0);
 
 // Host driver: runs `T` iterations (per job) of the sweep for every job in
 // `jobs` (any mix of N and M), lock-step by position: tick t performs the

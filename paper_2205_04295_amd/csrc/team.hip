@@ -68,7 +68,7 @@ constexpr int kSide = 2;          // transforms of a lane group side by side
 constexpr long long kMaxPositions = 65536;  // of a team in one launch (about 15 us each)
 constexpr unsigned kClosed = 0x40000000u;
 constexpr long long kFormTicks = 1000000;      // 10 ms of the 100 MHz wall clock
-constexpr long long kSpinTicks = 2000000000LL; // 20 s: a wait inside a job that ends so late is an error
+constexpr int kSpinTicks = 2000000000;         // 20 s: a wait inside a job that ends so late is an error
 constexpr long long kIdleTicks = 1000000000000LL;  // ... of members without work, for the others' job
 
 // One job as the teams read it, in the job's own workspace (psi[1], which the
@@ -87,17 +87,19 @@ constexpr size_t kJobOffset = kCtrlBytes;  // of TeamJob inside psi[1]
 constexpr size_t kFlagOffset = kJobOffset + 256;
 constexpr int kFlagWords = 3 * kMaxSize * 2;
 // control words: job queue heads, then per XCD 64 words: the arrival count,
-// the closed count, then (team k) the arrivals at its barrier between jobs
-// and the job it runs
+// the closed count, then for team k, on 8 bytes, the arrivals at its barrier
+// between jobs and the arrivals at which all members leave (0: not yet), and
+// the job it runs
 constexpr int kCtrlXcc = 64;
 constexpr int kXccWords = 64;
-static_assert((kCtrlXcc + kMaxXcc * kXccWords) * 4 <= kCtrlBytes && 2 + 2 * kMaxTeams <= kXccWords, "control words");
+static_assert((kCtrlXcc + kMaxXcc * kXccWords) * 4 <= kCtrlBytes && 2 + 4 * kMaxTeams <= kXccWords, "control words");
 static_assert(sizeof(TeamJob) <= 256 && kFlagOffset + kFlagWords * 4 <= 8192, "psi[1] of 32^2 x 1");
 
 struct TeamArgs {
   unsigned* ctrl;
   int expect;                    // workgroups of each XCD
   int limit;                     // ... of which teams are formed at most
+  int spin;                      // ticks after which a wait inside a job gives up
   int first[kClasses + 1];       // job[first[c] .. first[c + 1]) are class c's, longest first
   const TeamJob* job[kMaxTeamJobs];
 };
@@ -200,7 +202,7 @@ __device__ __forceinline__ int xcc_id() { return __builtin_amdgcn_s_getreg((3 <<
 // The members of a team as one of them sees it.
 struct Team {
   int rank, size;
-  unsigned* bar;     // arrivals, counted up; behind it the job being run
+  unsigned* bar;     // arrivals, counted up; behind it when to leave, and the job being run
   unsigned target;   // arrivals that end the next barrier
 };
 
@@ -230,19 +232,34 @@ struct Shared {
   float part[kMaxWaves];   // each wave's maximum
   float top;               // the team's
   int ok;                  // 0: a wait took too long, leave
+  int spin;                // (TeamArgs)
   int team, rank, size;
 };
 
-// Barrier over the workgroups of a team between jobs.
-__device__ __forceinline__ void team_barrier(Team& tm, Shared* sh) {
+// Barrier over the workgroups of a team between jobs.  False: leave.  A member
+// whose wait inside a job gave up says so before it arrives at the barrier that
+// ends the job, and by that barrier's number: a slower one may still be reading
+// at the barrier before it, which all must pass.  So all leave at the same one
+// and none waits for a member that has left.  (The bound of this wait is a last
+// resort: those it waits for are running, and their own waits end.)
+__device__ __forceinline__ bool team_barrier(Team& tm, Shared* sh) {
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   tm.target += (unsigned)tm.size;
   if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0) {
     add_one(tm.bar);
     const long long t0 = wall_clock64();
-    while ((int)(ld_uniform(tm.bar) - tm.target) < 0) {
+    for (;;) {
+      const unsigned long long v = __hip_atomic_load((const unsigned long long*)tm.bar, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
+      const unsigned here = __builtin_amdgcn_readfirstlane((unsigned)v);
+      const unsigned leave = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
+      if ((int)(here - tm.target) >= 0) {
+        if (leave && (int)(tm.target - leave) >= 0) sh->ok = 0;
+        break;
+      }
       if (wall_clock64() - t0 > kIdleTicks) {
+        st_agent(tm.bar + 1, tm.target);
         sh->ok = 0;
         break;
       }
@@ -250,6 +267,7 @@ __device__ __forceinline__ void team_barrier(Team& tm, Shared* sh) {
     }
   }
   __syncthreads();
+  return __builtin_amdgcn_readfirstlane(sh->ok) != 0;
 }
 
 // Barriers inside a job.  Barrier b (0, 1, 2: after the gather, the columns,
@@ -282,7 +300,7 @@ struct JobBarrier {
         for (;;) {
           v = one.ld_team<unsigned long long>();
           if (__builtin_amdgcn_ballot_w64((int)((unsigned)v - epoch) >= 0) == ~0ull) break;
-          if (wall_clock64() - t0 > kSpinTicks) {
+          if (wall_clock64() - t0 > __builtin_amdgcn_readfirstlane(sh->spin)) {
             sh->ok = 0;
             break;
           }
@@ -1064,6 +1082,14 @@ __device__ __forceinline__ void member(const TeamJob* t, int M, const Team& tm, 
   }
 }
 
+// A team that leaves: of the jobs that it might have run after this one, its
+// leader flags those that no other team has taken.
+__device__ __forceinline__ void give_up(const TeamArgs& a, const Team& tm, int c) {
+  if (tm.rank != 0 || threadIdx.x != 0) return;
+  for (; c < kClasses; ++c)
+    for (int q; (q = pop_job(a, c)) >= 0;) flag_status(a.job[q]->j.status, MRPIE_STATUS_UNFINISHED);
+}
+
 // N: the probe size of every job of the launch, 0: any mix.
 template <int N, int WV>
 __global__ __launch_bounds__(WV * 64, WV / 4) void k_team(const TeamArgs a) {
@@ -1073,6 +1099,7 @@ __global__ __launch_bounds__(WV * 64, WV / 4) void k_team(const TeamArgs a) {
   unsigned* const ctrl = a.ctrl + kCtrlXcc + x * kXccWords;
   if (threadIdx.x == 0) {
     sh.ok = 1;
+    sh.spin = a.spin;
     // arrive; the first on this XCD closes the list
     const unsigned t = add_agent(ctrl, 1u);
     unsigned n = 0;
@@ -1083,7 +1110,7 @@ __global__ __launch_bounds__(WV * 64, WV / 4) void k_team(const TeamArgs a) {
       n = __hip_atomic_fetch_or(ctrl, kClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       st_agent(ctrl + 1, n | kClosed);
     } else if (!(t & kClosed)) {
-      while (!((n = ld_agent(ctrl + 1)) & kClosed) && wall_clock64() - t0 < kSpinTicks) {
+      while (!((n = ld_agent(ctrl + 1)) & kClosed) && wall_clock64() - t0 < kIdleTicks) {
       }
       n &= ~kClosed;
     }
@@ -1096,13 +1123,12 @@ __global__ __launch_bounds__(WV * 64, WV / 4) void k_team(const TeamArgs a) {
   for (int c = 0; c < kClasses; ++c) {
     if (a.first[c + 1] == a.first[c]) continue;
     const int cap = kMaxSize >> c, team = me / cap;
-    Team tm{me - team * cap, min(cap, there - team * cap), ctrl + 2 + 2 * ((1 << c) - 1 + team), 0u};
+    Team tm{me - team * cap, min(cap, there - team * cap), ctrl + 2 + 4 * ((1 << c) - 1 + team), 0u};
     if (team >= 1 << c) continue;  // more workgroups than teams
     for (;;) {
-      if (tm.rank == 0 && threadIdx.x == 0) st_agent(tm.bar + 1, (unsigned)pop_job(a, c));
-      team_barrier(tm, &sh);
-      if (!__builtin_amdgcn_readfirstlane(sh.ok)) return;
-      const int q = (int)ld_uniform(tm.bar + 1);
+      if (tm.rank == 0 && threadIdx.x == 0) st_agent(tm.bar + 2, (unsigned)pop_job(a, c));
+      if (!team_barrier(tm, &sh)) return give_up(a, tm, c);
+      const int q = (int)ld_uniform(tm.bar + 2);
       if (q < 0) break;
       const TeamJob* t = a.job[q];
       const MRPIE_AS4 TeamJob* tj = (const MRPIE_AS4 TeamJob*)(unsigned long long)t;
@@ -1125,12 +1151,12 @@ __global__ __launch_bounds__(WV * 64, WV / 4) void k_team(const TeamArgs a) {
         default: go(std::integral_constant<int, N ? N : 256>{}); break;
       }
       // (every member is past the job's last barrier before the leader's next
-      // pop is read, and reads tm.bar + 1 before it can arrive at that barrier)
-      team_barrier(tm, &sh);
+      // pop is read, and reads tm.bar + 2 before it can arrive at that barrier)
       if (!__builtin_amdgcn_readfirstlane(sh.ok)) {
-        if (tm.rank == 0) flag_status(tj->j.status, MRPIE_STATUS_NONFINITE);
-        return;
+        st_agent(tm.bar + 1, tm.target + (unsigned)tm.size);
+        flag_status(tj->j.status, MRPIE_STATUS_UNFINISHED);
       }
+      if (!team_barrier(tm, &sh)) return give_up(a, tm, c);
     }
   }
 }
@@ -1226,10 +1252,12 @@ bool team_suits(int N, int M, int njobs) {
 
 bool team_fits(int N, int M) { return job_km(N, M, N == 256 && M == 3 ? 12 : 8, kMaxSize) > 0; }
 
-int run_team(const Common& c, const JobRec* jobs, int njobs, float* const* err_out, hipStream_t s, int limit) {
+int run_team(const Common& c, const JobRec* jobs, int njobs, float* const* err_out, hipStream_t s, int limit,
+             int wait_ns) {
   if (njobs > kMaxTeamJobs) {
     for (int b = 0; b < njobs; b += kMaxTeamJobs) {
-      const int rc = run_team(c, jobs + b, std::min(kMaxTeamJobs, njobs - b), err_out ? err_out + b : nullptr, s, limit);
+      const int rc = run_team(c, jobs + b, std::min(kMaxTeamJobs, njobs - b), err_out ? err_out + b : nullptr, s, limit,
+                              wait_ns);
       if (rc) return rc;
     }
     return MRPIE_OK;
@@ -1261,7 +1289,7 @@ int run_team(const Common& c, const JobRec* jobs, int njobs, float* const* err_o
         part[n].T = std::min(most, jobs[b].T - it);
         err[n++] = err_out && err_out[b] ? err_out[b] + it : nullptr;
       }
-      const int rc = run_team(ci, part.data(), n, err.data(), s, limit);
+      const int rc = run_team(ci, part.data(), n, err.data(), s, limit, wait_ns);
       if (rc) return rc;
     }
     return MRPIE_OK;
@@ -1301,6 +1329,7 @@ int run_team(const Common& c, const JobRec* jobs, int njobs, float* const* err_o
   // a call with a team for every job needs no more workgroups than those
   a.expect = njobs <= nxcc ? kMaxSize >> *std::min_element(cls.begin(), cls.end()) : kMaxSize;
   a.limit = limit;
+  a.spin = wait_ns ? (int)((wait_ns + 9LL) / 10) : kSpinTicks;  // ticks of 10 ns
   const TeamLaunch tl = team_kernel(N, waves);
   MRPIE_HIP(ensure_lds((const void*)tl.k, tl.lds));
   int rc = launch_init_twiddles(s);

@@ -21,13 +21,13 @@ def _gpu():
     need_gpu()
 
 
-def team(ws, members, **prm):
+def team(ws, members, wait_ns=0, **prm):
     from paper_2205_04295_amd import api
     devs = [to_dev(w) for w in ws]
     jobs = [dict(obj=d["obj"], probe=d["probe"], pos=d["pos"], intens=d["I"],
                  err=torch.zeros(prm["iterations"], dtype=torch.float32, device="cuda:0"),
                  status=torch.zeros(1, dtype=torch.int32, device="cuda:0")) for d in devs]
-    api.team_sweep(jobs, members=members, **prm)
+    api.team_sweep(jobs, members=members, wait_ns=wait_ns, **prm)
     torch.cuda.synchronize()
     return [dict(O=j["obj"].cpu().numpy(), P=j["probe"].cpu().numpy(), err=j["err"].cpu().numpy(),
                  status=int(j["status"].item())) for j in jobs]
@@ -62,3 +62,20 @@ def test_small_teams_of_mixed_sizes(members):
     ws = [wl.small_case(820 + i, N + 21, N, M, 3 + i % 2, W=N + 12, name=f"x{i}") for i, (N, M) in enumerate(specs)]
     ws[3].pos0[1] = (999.0, -4.0)  # clamped and flagged in both
     check(ws, members, dict(EPIE, iterations=2, probe_update_start=1))
+
+
+@pytest.mark.parametrize("N,M,jobs,members", [(256, 3, 3, 32), (128, 2, 20, 32), (64, 2, 1, 32), (256, 1, 12, 5)])
+def test_wait_that_gives_up(N, M, jobs, members):
+    """Waits inside a job that give up at once: the launch ends, a
+    job is either swept as ever or flagged as unfinished, whichever member
+    gave up and whoever had no part in it, and the next call is unharmed."""
+    ws = [wl.small_case(860 + b % 2, N + 19, N, M, 60, W=N + 26, name=f"w{b % 2}") for b in range(jobs)]
+    prm = dict(EPIE, iterations=2)
+    ref = team(ws, members, **prm)
+    got = team(ws, members, wait_ns=1, **prm)
+    print([g["status"] for g in got])
+    assert any(g["status"] == 4 for g in got)
+    for a, b in zip(got, ref):
+        assert a["status"] == 4 or (a["status"] == 0 and np.array_equal(a["O"], b["O"]))
+    for a, b in zip(team(ws, members, **prm), ref):
+        assert a["status"] == 0 and np.array_equal(a["O"], b["O"]) and np.array_equal(a["P"], b["P"])
