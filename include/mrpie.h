@@ -234,6 +234,21 @@ typedef struct {
 int mrpie_set_tuning(int32_t N, int32_t M, int32_t batched, const mrpie_tuning* t);
 int mrpie_get_tuning(int32_t N, int32_t M, int32_t batched, mrpie_tuning* t);
 
+/* Whether calls of that size, mode class and call class run as launches of the
+ * installed (or default) tuning or as one persistent launch:
+ * MRPIE_ROUTE_AUTO leaves it to the library (see mrpie_rpie_batched).
+ * mrpie_set_tuning sets MRPIE_ROUTE_LAUNCHES, or MRPIE_ROUTE_AUTO if the
+ * tuning is the default; mrpie_autotune sets what it found faster.  A program
+ * that restores or reloads a tuning does so with mrpie_set_tuning and then
+ * mrpie_set_route.  Calls whose largest probe has the launches' route run as
+ * launches, and so does what no persistent launch holds (256^2 x 7 or 8).
+ * Process-wide host state like the tuning. */
+#define MRPIE_ROUTE_AUTO 0
+#define MRPIE_ROUTE_LAUNCHES 1
+#define MRPIE_ROUTE_PERSISTENT 2
+int mrpie_set_route(int32_t N, int32_t M, int32_t batched, int32_t route);
+int mrpie_get_route(int32_t N, int32_t M, int32_t batched, int32_t* route);
+
 /* Batched M-rPIE: runs mrpie_rpie's sweep (same parameters for every job;
  * refine, subpixel and propagator must be 0, else MRPIE_EUNSUPPORTED) on
  * `njobs` independent reconstructions of any mix of N, M, J and object
@@ -278,8 +293,8 @@ int mrpie_rpie_batched(int32_t njobs, const mrpie_job* jobs, const mrpie_params*
  * installs the best
  * candidate for that (N, mode class, batch class) as mrpie_set_tuning
  * would, and returns it in *best (may be NULL).  The persistent launch is
- * timed too; where it is faster than every candidate it stays the default.  cand_ms (may be NULL)
- * receives each candidate's time in ms.  The call waits on the host for its
+ * timed too; calls of that class then run as whichever was faster
+ * (mrpie_get_route).  cand_ms (may be NULL) receives each candidate's time in ms.  The call waits on the host for its
  * timing events, so it may not be captured into a graph; it allocates no
  * device memory (workspace: mrpie_autotune_workspace_size bytes, reps in
  * [1, 100]).  mrpie_tuning_candidates writes up to `cap` candidates to

@@ -82,6 +82,8 @@ _SIGS = {
     "mrpie_team_sweep": (C.c_int, [C.c_int32, C.c_void_p, C.POINTER(Params), C.c_int32, C.c_int32, _P]),
     "mrpie_set_tuning": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.POINTER(Tuning)]),
     "mrpie_get_tuning": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.POINTER(Tuning)]),
+    "mrpie_set_route": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.c_int32]),
+    "mrpie_get_route": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)]),
     "mrpie_tuning_candidates": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.POINTER(Tuning), C.c_int32]),
     "mrpie_autotune_workspace_size": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.c_int32,
                                                 C.POINTER(C.c_size_t)]),

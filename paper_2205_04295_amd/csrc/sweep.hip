@@ -1192,7 +1192,8 @@ __global__ void k_probe_back(const LaunchArgs a) {
 // single-job kernels' register capacities; the multi-job kernels split the
 // last class into 5-6 and 7-8).
 static Tuning g_tune[5][4][3];
-static bool g_tune_set[5][4][3], g_tune_team[5][4][3];
+static bool g_tune_set[5][4][3];
+static int g_route[5][4][3];
 static std::mutex g_tune_mu;
 
 // Call classes: a single job, batches of 2 to kLargeBatch - 1 jobs, larger
@@ -1216,6 +1217,12 @@ Tuning get_tuning(int N, int M, int nb) {
   return default_tuning(N, nb);
 }
 
+static bool same_tuning(const Tuning& a, const Tuning& b) {
+  return a.rows_radix == b.rows_radix && a.cols_radix == b.cols_radix && a.rows_threads == b.rows_threads &&
+         a.lds_sweep == b.lds_sweep && a.cols_width == b.cols_width && a.rows_inplace == b.rows_inplace &&
+         a.rows_split == b.rows_split;
+}
+
 void set_tuning(int N, int M, int nb, const Tuning& t) {
   const int ni = n_index(N), bc = batch_class(nb);
   if (ni < 0) return;
@@ -1224,28 +1231,22 @@ void set_tuning(int N, int M, int nb, const Tuning& t) {
     if (M <= 0 || mi == mode_index(M)) {
       g_tune[ni][mi][bc] = t;
       g_tune_set[ni][mi][bc] = true;
-      g_tune_team[ni][mi][bc] = false;
+      g_route[ni][mi][bc] = same_tuning(t, default_tuning(N, nb)) ? MRPIE_ROUTE_AUTO : MRPIE_ROUTE_LAUNCHES;
     }
 }
 
-static bool same_tuning(const Tuning& a, const Tuning& b) {
-  return a.rows_radix == b.rows_radix && a.cols_radix == b.cols_radix && a.rows_threads == b.rows_threads &&
-         a.lds_sweep == b.lds_sweep && a.cols_width == b.cols_width && a.rows_inplace == b.rows_inplace &&
-         a.rows_split == b.rows_split;
-}
-
-bool tuned(int N, int M, int nb) {
+int get_route(int N, int M, int nb) {
   const int ni = n_index(N), mi = mode_index(M), bc = batch_class(nb);
   std::lock_guard<std::mutex> lk(g_tune_mu);
-  return ni >= 0 && g_tune_set[ni][mi][bc] && !g_tune_team[ni][mi][bc] &&
-         !same_tuning(g_tune[ni][mi][bc], default_tuning(N, nb));
+  return ni < 0 ? MRPIE_ROUTE_AUTO : g_route[ni][mi][bc];
 }
 
-void prefer_team(int N, int M, int nb) {
-  const int ni = n_index(N), mi = mode_index(M), bc = batch_class(nb);
+void set_route(int N, int M, int nb, int route) {
+  const int ni = n_index(N), bc = batch_class(nb);
   if (ni < 0) return;
   std::lock_guard<std::mutex> lk(g_tune_mu);
-  g_tune_team[ni][mi][bc] = true;
+  for (int mi = 0; mi < 4; ++mi)
+    if (M <= 0 || mi == mode_index(M)) g_route[ni][mi][bc] = route;
 }
 
 // ------------------------------------------------------------ host driver
@@ -1511,9 +1512,10 @@ static int run_passes(const Common& c, const JobRec* jobs, int njobs, float* con
 }
 
 // Which jobs of a call run in teams (team.hip).  A tuning that the caller
-// passed, or installed for a job's size or the call's largest, asks for
-// launches of that shape: such a job goes to a team only if the tuning's lds_sweep says so.  The others go
-// where team_suits() has them; a call of mixed probe sizes goes to the teams
+// passed, or the launches' route of a job's size or of the call's largest, asks
+// for launches of that shape: such a job goes to a team only if the tuning's
+// lds_sweep says so.  Those whose route is the persistent launch take it.  The
+// others go where team_suits() has them; a call of mixed probe sizes goes to the teams
 // as a whole unless most of its work does not suit them (64 uneven jobs of
 // 64^2 to 256^2: 9.9 ms in teams, 11.8 ms in launches, 192^2 jobs included).
 static void choose_team(const JobRec* jobs, int njobs, const Tuning* force, std::vector<char>& team) {
@@ -1524,15 +1526,20 @@ static void choose_team(const JobRec* jobs, int njobs, const Tuning* force, std:
     maxN = std::max(maxN, jobs[b].N);
     maxM = std::max(maxM, jobs[b].M);
   }
-  const bool asked = force || tuned(maxN, maxM, njobs);
+  const bool asked = force || get_route(maxN, maxM, njobs) == MRPIE_ROUTE_LAUNCHES;
   team.assign(njobs, 0);
   std::vector<char> free_choice(njobs, 0);
   for (int b = 0; b < njobs; ++b) {
     const JobRec& jb = jobs[b];
     if (!team_fits(jb.N, jb.M)) continue;
-    if (asked || tuned(jb.N, jb.M, njobs)) {
+    const int route = get_route(jb.N, jb.M, njobs);
+    if (asked || route == MRPIE_ROUTE_LAUNCHES) {
       const int most = force ? force->lds_sweep : get_tuning(jb.N, jb.M, njobs).lds_sweep;
       team[b] = jb.M <= most && lds_sweep_fits(jb.N, jb.M);
+      continue;
+    }
+    if (route == MRPIE_ROUTE_PERSISTENT) {
+      team[b] = 1;
       continue;
     }
     free_choice[b] = 1;
@@ -1747,6 +1754,24 @@ int mrpie_set_tuning(int32_t N, int32_t M, int32_t batched, const mrpie_tuning* 
   set_tuning(N, M, batch_class_jobs(batched),
              Tuning{t->rows_radix, t->cols_radix, t->rows_threads, t->lds_sweep, t->cols_width, t->rows_inplace,
                     t->rows_split});
+  return MRPIE_OK;
+}
+
+int mrpie_set_route(int32_t N, int32_t M, int32_t batched, int32_t route) {
+  if (n_index(N) < 0) return fail(MRPIE_EUNSUPPORTED, "N=%d not in {32,64,128,192,256}", N);
+  if (batched < 0 || batched > 2) return fail(MRPIE_EINVAL, "batched=%d not in {0, 1, 2}", batched);
+  if (M < 0 || M > MRPIE_MAX_MODES) return fail(MRPIE_EINVAL, "M=%d not in [0, 8]", M);
+  if (route < MRPIE_ROUTE_AUTO || route > MRPIE_ROUTE_PERSISTENT) return fail(MRPIE_EINVAL, "route=%d not in [0, 2]", route);
+  set_route(N, M, batch_class_jobs(batched), route);
+  return MRPIE_OK;
+}
+
+int mrpie_get_route(int32_t N, int32_t M, int32_t batched, int32_t* route) {
+  if (n_index(N) < 0) return fail(MRPIE_EUNSUPPORTED, "N=%d not in {32,64,128,192,256}", N);
+  if (batched < 0 || batched > 2) return fail(MRPIE_EINVAL, "batched=%d not in {0, 1, 2}", batched);
+  if (M < 1 || M > MRPIE_MAX_MODES) return fail(MRPIE_EINVAL, "M=%d not in [1, 8]", M);
+  if (!route) return fail(MRPIE_EINVAL, "route is NULL");
+  *route = get_route(N, M, batch_class_jobs(batched));
   return MRPIE_OK;
 }
 

@@ -80,11 +80,11 @@ struct Tuning {
 // for it, else the default.  set_tuning with M = 0 sets every mode class.
 Tuning get_tuning(int N, int M, int nb);
 void set_tuning(int N, int M, int nb, const Tuning& t);
-// Whether a tuning other than the default is installed there that asks for
-// launches of that shape; prefer_team(true) withdraws the request (the tuning
-// stays readable) until the next set_tuning.
-bool tuned(int N, int M, int nb);
-void prefer_team(int N, int M, int nb);
+// The route (MRPIE_ROUTE_*) of such calls.  set_tuning sets it: launches, or
+// the library's own choice for the default tuning, which a program that
+// restores what get_tuning gave it installs.
+int get_route(int N, int M, int nb);
+void set_route(int N, int M, int nb, int route);
 inline bool lds_sweep_fits(int N, int M) { return N <= 128 && M * N * N <= 16384; }
 Tuning default_tuning(int N, int nb);
 // A job count of call class cls (0: one job, 1: 2-15 jobs, 2: 16 or more).

@@ -191,7 +191,7 @@ int mrpie_autotune(int32_t N, int32_t M, int32_t batch, int32_t J, int32_t reps,
   if (rc != MRPIE_OK || best_i < 0) return rc ? rc : fail(MRPIE_EDEVICE, "no candidate ran");
   const Tuning& t = cands[best_i];
   set_tuning(N, M, nb, t);
-  if (nt > n && t_best[n] <= best_ms) prefer_team(N, M, nb);
+  set_route(N, M, nb, nt > n && t_best[n] <= best_ms ? MRPIE_ROUTE_PERSISTENT : MRPIE_ROUTE_LAUNCHES);
   if (best)
     *best = mrpie_tuning{t.rows_radix, t.cols_radix, t.rows_threads, t.lds_sweep, t.cols_width, t.rows_inplace,
                          t.rows_split};

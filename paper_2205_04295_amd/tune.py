@@ -66,9 +66,26 @@ def get_tuning(N, batched, M=1):
     return _as_dict(t)
 
 
+ROUTES = ("auto", "launches", "persistent")
+
+
+def set_route(N, batched, route, M=0):
+    """Run calls of (N, mode class of M, batch class) as "launches" of the
+    installed tuning, as one "persistent" launch, or leave it to the library
+    ("auto").  set_tuning sets it too: set the route after it."""
+    _abi.check(_abi.load().mrpie_set_route(N, M, int(batched), ROUTES.index(route)))
+
+
+def get_route(N, batched, M=1):
+    r = C.c_int32(0)
+    _abi.check(_abi.load().mrpie_get_route(N, M, int(batched), C.byref(r)))
+    return ROUTES[r.value]
+
+
 def autotune(N, M, batch=1, J=64, reps=3, device="cuda:0", stream=None):
     """Time every candidate launch shape on a synthetic (N, M) sweep of J
-    positions with `batch` jobs (mrpie_autotune) and install the fastest.
+    positions with `batch` jobs (mrpie_autotune) and install the fastest, and
+    as the route the faster of it and the persistent launch.
     Returns (best, {candidate tuple: ms})."""
     lib = _abi.load()
     n = C.c_size_t(0)
