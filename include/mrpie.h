@@ -266,8 +266,14 @@ int mrpie_get_route(int32_t N, int32_t M, int32_t batched, int32_t* route);
  * only read and may be shared; so may status words).
  * Each job's object and probe match those of a mrpie_rpie call on that job
  * alone to float rounding; the error curve may differ in the summation
- * order of its partial sums.  Persistent launches of one device run one at a
- * time: a call on another stream waits for the last one (not under capture).
+ * order of its partial sums.  A call of fewer jobs than the device has XCDs
+ * (8) takes one XCD for each job and of it only the CUs that the job's units
+ * fill; other calls take all.  Calls on several streams run side by side on
+ * different XCDs and one after the other on the same (they wait for an event
+ * of the last launch there; the first call on a device creates 17 events, kept
+ * until the process ends).  Captured launches take the XCDs in turn but can't
+ * wait: graphs replayed at the same time on the same XCDs share the CUs, which
+ * gives the same results after a wait of 10 ms and at a fraction of the speed.
  * Of two or more jobs for the lock-step launches every second one runs
  * on an internal non-blocking stream (default priority; the first such call
  * on a device creates it and 16 events, kept until the process ends),

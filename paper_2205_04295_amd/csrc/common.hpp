@@ -42,8 +42,8 @@ inline int n_index(int N) {
 static __device__ float2 g_tw[5][256];
 static __device__ double2 g_tw64[5][256];
 
-static __global__ void k_init_twiddles() {
-  const int idx = blockIdx.x;
+static __global__ void k_init_twiddles(int first) {
+  const int idx = first + blockIdx.x;
   const int N = idx == 0 ? 64 : idx == 1 ? 128 : idx == 2 ? 192 : idx == 3 ? 256 : 32;
   for (int e = threadIdx.x; e < N; e += blockDim.x) {
     double s, c;
@@ -53,8 +53,9 @@ static __global__ void k_init_twiddles() {
   }
 }
 
-static inline int launch_init_twiddles(hipStream_t s) {
-  hipLaunchKernelGGL(k_init_twiddles, dim3(5), dim3(256), 0, s);
+// of all sizes, or of the one with that n_index
+static inline int launch_init_twiddles(hipStream_t s, int only = -1) {
+  hipLaunchKernelGGL(k_init_twiddles, dim3(only < 0 ? 5 : 1), dim3(256), 0, s, only < 0 ? 0 : only);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "k_init_twiddles");
   return MRPIE_OK;

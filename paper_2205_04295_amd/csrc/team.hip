@@ -100,6 +100,7 @@ struct TeamArgs {
   int expect;                    // workgroups of each XCD
   int limit;                     // ... of which teams are formed at most
   int spin;                      // ticks after which a wait inside a job gives up
+  int nxcc, from, xccs;          // XCDs of the device, the first of the launch and how many of them
   int first[kClasses + 1];       // job[first[c] .. first[c + 1]) are class c's, longest first
   const TeamJob* job[kMaxTeamJobs];
 };
@@ -1095,6 +1096,8 @@ template <int N, int WV>
 __global__ __launch_bounds__(WV * 64, WV / 4) void k_team(const TeamArgs a) {
   extern __shared__ __align__(16) char lds[];
   __shared__ Shared sh;
+  // workgroups go to the XCDs in turn
+  if ((blockIdx.x + (unsigned)(a.nxcc - a.from)) % (unsigned)a.nxcc >= (unsigned)a.xccs) return;
   const int x = xcc_id();
   unsigned* const ctrl = a.ctrl + kCtrlXcc + x * kXccWords;
   if (threadIdx.x == 0) {
@@ -1217,6 +1220,13 @@ int job_need(int N, int M, int waves, int km) {
   while (uw * 2 * mw <= waves) uw *= 2;
   return (N / G + uw - 1) / uw;
 }
+// Members that take part in it: as many as its units keep busy (Deal's).
+int job_members(int N, int M, int waves, int km) {
+  const int G = N == 256 ? 2 : N == 192 || N == 128 ? 4 : N == 64 ? 8 : 16, mw = (M + km - 1) / km;
+  int uw = 1;
+  while (uw * 2 * mw <= waves && uw * kMaxSize < N / G) uw *= 2;
+  return (N / G + uw - 1) / uw;
+}
 // Modes of a wave: as few as let a team of `cap` hold the job, or as few as
 // any team can.
 int job_km(int N, int M, int waves, int cap) {
@@ -1230,11 +1240,92 @@ int job_km(int N, int M, int waves, int cap) {
 }  // namespace
 
 
-static std::mutex& team_mutex() {
-  static std::mutex mu;
-  return mu;
+// Launches on the same XCD run one at a time: two that each held half of its
+// CUs would wait for members until their lists close.  A call of fewer jobs
+// than XCDs takes one XCD for each, so calls on several streams run side by
+// side: a stream keeps the XCDs it last used, or takes idle ones, or queues
+// behind the last launch on others, the highest first: workgroups go to the
+// XCDs in turn from the first, so kernels of a few workgroups (the next call's
+// setup among them) find room on the lower ones.  An event of each launch is kept for the
+// XCDs that it was the last on.
+namespace {
+constexpr int kMaxDevices = 16;  // (on further ones nothing is queued)
+struct Turns {
+  hipEvent_t ev[kMaxXcc + 1] = {};
+  int last[kMaxXcc];             // event of the last launch on each XCD, -1: none
+  hipStream_t by[kMaxXcc] = {};  // its stream, only ever compared
+  unsigned next = 0;             // taken downwards from here
+  bool ready = false;
+};
+Turns g_turns[kMaxDevices];
+std::mutex g_turns_mu;
+
+int init_turns(Turns& t) {
+  if (t.ready) return MRPIE_OK;
+  for (hipEvent_t& e : t.ev)
+    if (!e) MRPIE_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+  std::fill(t.last, t.last + kMaxXcc, -1);
+  t.ready = true;
+  return MRPIE_OK;
 }
-constexpr int kTeamEvent = kSideEvents - 1;
+
+// The first of `n` adjacent XCDs for a launch on `s`.
+int pick_xccs(Turns& t, int n, int nxcc, hipStream_t s) {
+  const auto own = [&](int x) { return t.last[x] >= 0 && t.by[x] == s; };
+  int cost[kMaxXcc];
+  for (int i = 0; i < nxcc; ++i) {
+    bool all = true;
+    for (int k = 0; k < n; ++k) all &= own((i + k) % nxcc);
+    if (all) return i;
+  }
+  // (an event may be queried while another thread captures a graph)
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  for (int x = 0; x < nxcc; ++x)
+    cost[x] = own(x) ? 0 : t.last[x] < 0 || hipEventQuery(t.ev[t.last[x]]) == hipSuccess ? 1 : 2 * nxcc;
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (hipPeekAtLastError() == hipErrorNotReady) (void)hipGetLastError();  // it is none
+  int best = 0, least = INT32_MAX;
+  for (int i = 0; i < nxcc; ++i) {
+    const int from = (int)((t.next + 2 * nxcc - n - i) % nxcc);
+    int c = 0;
+    for (int k = 0; k < n; ++k) c += cost[(from + k) % nxcc];
+    if (c < least) {
+      least = c;
+      best = from;
+    }
+  }
+  t.next = (unsigned)best;
+  return best;
+}
+
+// Queues `s` behind the last launches on those XCDs.
+int wait_turn(const Turns& t, int from, int n, int nxcc, hipStream_t s) {
+  unsigned waited = 0;
+  for (int k = 0; k < n; ++k) {
+    const int e = t.last[(from + k) % nxcc];
+    if (e < 0 || (waited >> e & 1)) continue;
+    waited |= 1u << e;
+    MRPIE_HIP(hipStreamWaitEvent(s, t.ev[e], 0));
+  }
+  return MRPIE_OK;
+}
+
+// What was launched on `s` is the last on them.
+int record_turn(Turns& t, int from, int n, int nxcc, hipStream_t s) {
+  unsigned used = 0;
+  for (int k = 0; k < n; ++k) t.last[(from + k) % nxcc] = -1;
+  for (int x = 0; x < nxcc; ++x)
+    if (t.last[x] >= 0) used |= 1u << t.last[x];
+  const int e = __builtin_ctz(~used);
+  MRPIE_HIP(hipEventRecord(t.ev[e], s));
+  for (int k = 0; k < n; ++k) {
+    t.last[(from + k) % nxcc] = e;
+    t.by[(from + k) % nxcc] = s;
+  }
+  return MRPIE_OK;
+}
+}  // namespace
 
 // Whether a call of `njobs` jobs, of this size each, is for the teams rather
 // than the launches of sweep.hip.  Measured in us a position of the card
@@ -1265,8 +1356,8 @@ int run_team(const Common& c, const JobRec* jobs, int njobs, float* const* err_o
   int dev = 0, cus = 0;
   MRPIE_HIP(hipGetDevice(&dev));
   MRPIE_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-  const int nxcc = std::max(1, cus / 32);
-  // A launch holds the CUs' LDS, so it ends after about a second's work and
+  const int nxcc = std::min(kMaxXcc, std::max(1, cus / 32));
+  // A launch holds its members' CUs, so it ends after about a second's work and
   // lets other streams' kernels in; the next resumes with the same bits.
   long long longest = 1, all = 0;
   int T = 0;
@@ -1326,28 +1417,39 @@ int run_team(const Common& c, const JobRec* jobs, int njobs, float* const* err_o
     a.first[cls[order[i]] + 1] = i + 1;
   }
   for (int k = 1; k <= kClasses; ++k) a.first[k] = std::max(a.first[k], a.first[k - 1]);
-  // a call with a team for every job needs no more workgroups than those
-  a.expect = njobs <= nxcc ? kMaxSize >> *std::min_element(cls.begin(), cls.end()) : kMaxSize;
+  // A call with an XCD for every job needs no more workgroups than its jobs'
+  // members, and leaves the other CUs and XCDs free.
+  a.nxcc = nxcc;
+  a.xccs = std::min(njobs, nxcc);
+  a.expect = kMaxSize;
+  if (njobs <= nxcc) {
+    a.expect = 1;
+    for (int b = 0; b < njobs; ++b)
+      a.expect = std::max(a.expect, job_members(jobs[b].N, jobs[b].M, waves, km[b]));
+  }
   a.limit = limit;
   a.spin = wait_ns ? (int)((wait_ns + 9LL) / 10) : kSpinTicks;  // ticks of 10 ns
   const TeamLaunch tl = team_kernel(N, waves);
   MRPIE_HIP(ensure_lds((const void*)tl.k, tl.lds));
-  int rc = launch_init_twiddles(s);
+  int rc = launch_init_twiddles(s, n_index(N));
   if (rc) return rc;
-  // One such launch at a time on a device: two that each held half of the
-  // CUs would wait for members until their lists close.  Launches on other
-  // streams wait for the last one's event (not under capture, where a stream
-  // can't wait for work outside the graph).
+  // (A stream under capture can't wait for work outside its graph; captured
+  // launches take the XCDs in turn.)
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   MRPIE_HIP(hipStreamIsCapturing(s, &cap));
-  hipStream_t side = nullptr;
-  hipEvent_t* ev = nullptr;
-  std::unique_lock<std::mutex> lk;
-  if (cap == hipStreamCaptureStatusNone) {
-    rc = side_stream(&side, &ev);
+  const bool queue = cap == hipStreamCaptureStatusNone && dev < kMaxDevices;
+  Turns& turns = g_turns[dev < kMaxDevices ? dev : 0];
+  std::unique_lock<std::mutex> lk(g_turns_mu);
+  if (queue) {
+    rc = init_turns(turns);
     if (rc) return rc;
-    lk = std::unique_lock<std::mutex>(team_mutex());
-    MRPIE_HIP(hipStreamWaitEvent(s, ev[kTeamEvent], 0));
+    a.from = pick_xccs(turns, a.xccs, nxcc, s);
+    rc = wait_turn(turns, a.from, a.xccs, nxcc, s);
+    if (rc) return rc;
+  } else {
+    a.from = (int)((turns.next + 2 * nxcc - a.xccs) % nxcc);
+    turns.next = (unsigned)a.from;
+    lk.unlock();
   }
   for (int b = 0; b < njobs; b += kMaxJobsPerLaunch) {
     SetupArgs u{};
@@ -1365,8 +1467,7 @@ int run_team(const Common& c, const JobRec* jobs, int njobs, float* const* err_o
   for (int b = 0; b < njobs; ++b) positions += (long long)jobs[b].J * jobs[b].T;
   launch_ku(TK_TEAM, (int)std::min<long long>(positions, INT32_MAX), tl.k, dim3(a.expect * nxcc), dim3(waves * 64), tl.lds, s, a);
   MRPIE_HIP(hipGetLastError());
-  if (ev) MRPIE_HIP(hipEventRecord(ev[kTeamEvent], s));
-  return MRPIE_OK;
+  return queue ? record_turn(turns, a.from, a.xccs, nxcc, s) : MRPIE_OK;
 }
 
 }  // namespace mrpie
