@@ -274,6 +274,9 @@ int mrpie_get_route(int32_t N, int32_t M, int32_t batched, int32_t* route);
  * until the process ends).  Captured launches take the XCDs in turn but can't
  * wait: graphs replayed at the same time on the same XCDs share the CUs, which
  * gives the same results after a wait of 10 ms and at a fraction of the speed.
+ * While a launch runs, kernels of other streams find room only on CUs that it
+ * leaves free, so a call is cut into launches of about 1024 positions of a team
+ * (6 to 15 ms), or of one iteration if that is longer.
  * Of two or more jobs for the lock-step launches every second one runs
  * on an internal non-blocking stream (default priority; the first such call
  * on a device creates it and 16 events, kept until the process ends),

@@ -65,7 +65,7 @@ constexpr int kClasses = 4;
 constexpr int kMaxTeams = 15;     // teams of an XCD over all classes: 1 + 2 + 4 + 8
 constexpr int kMaxTeamJobs = 384; // jobs of one launch (pointers in the kernel arguments)
 constexpr int kSide = 2;          // transforms of a lane group side by side
-constexpr long long kMaxPositions = 65536;  // of a team in one launch (about 15 us each)
+constexpr long long kMaxPositions = 1024;   // of a team in one launch (6 to 15 us each)
 constexpr unsigned kClosed = 0x40000000u;
 constexpr long long kFormTicks = 1000000;      // 10 ms of the 100 MHz wall clock
 constexpr int kSpinTicks = 2000000000;         // 20 s: a wait inside a job that ends so late is an error
@@ -1357,8 +1357,9 @@ int run_team(const Common& c, const JobRec* jobs, int njobs, float* const* err_o
   MRPIE_HIP(hipGetDevice(&dev));
   MRPIE_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   const int nxcc = std::min(kMaxXcc, std::max(1, cus / 32));
-  // A launch holds its members' CUs, so it ends after about a second's work and
-  // lets other streams' kernels in; the next resumes with the same bits.
+  // A launch holds its members' CUs, so it ends after about 15 ms' work (or an
+  // iteration, if that is longer) and lets other streams' kernels in; the next
+  // resumes with the same bits.
   long long longest = 1, all = 0;
   int T = 0;
   for (int b = 0; b < njobs; ++b) {

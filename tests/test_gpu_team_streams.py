@@ -1,6 +1,6 @@
 """Persistent sweeps on several streams: calls of fewer jobs than XCDs run side
-by side and give the bits of calls made alone, captured calls may be replayed
-side by side."""
+by side and give the bits of calls made alone, a long call lets other streams'
+kernels in between its launches, captured calls may be replayed side by side."""
 import time
 
 import pytest
@@ -70,6 +70,23 @@ def test_two_streams_run_side_by_side(N, M, J, T):
     one, two = took(1), took(2)
     print(f"{N}^2 x {M}: one {one * 1e3:.2f} ms, two {two * 1e3:.2f} ms")
     assert two < 1.5 * one
+
+
+def test_long_call_lets_other_kernels_in():
+    j = job(256, 3, 100)
+    x = torch.ones(1 << 24, device="cuda")
+    s, other = torch.cuda.Stream(), torch.cuda.Stream()
+    run(j, s, 1)
+    with torch.cuda.stream(other):
+        x.mul_(2.0)
+    torch.cuda.synchronize()
+    run(j, s, 60)                   # 6000 positions, some 85 ms
+    with torch.cuda.stream(other):
+        x.mul_(2.0)                 # workgroups for every XCD
+    other.synchronize()
+    assert not s.query()            # ... were done before the call was
+    torch.cuda.synchronize()
+    assert float(x[123]) == 4.0
 
 
 def test_batches_of_several_sizes_on_four_streams():
