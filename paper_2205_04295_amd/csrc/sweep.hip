@@ -1515,11 +1515,24 @@ static int run_passes(const Common& c, const JobRec* jobs, int njobs, float* con
 // passed, or the launches' route of a job's size or of the call's largest, asks
 // for launches of that shape: such a job goes to a team only if the tuning's
 // lds_sweep says so.  Those whose route is the persistent launch take it.  The
-// others go where team_suits() has them; a call of mixed probe sizes goes to the teams
-// as a whole unless most of its work does not suit them (64 uneven jobs of
-// 64^2 to 256^2: 9.9 ms in teams, 11.8 ms in launches, 192^2 jobs included).
+// others run one way together: one after the other, launches and teams each
+// take as long as their longest chain (192^2 x 4 and x 5, a job each, 30
+// positions: 0.79 ms as launches, 1.12 ms one way each; 256^2 x 3 and x 8 1.08,
+// 1.30 ms).  They go where team_suits() has all of them or most of their work:
+//   one probe size  teams while at most a third of the work does not suit them:
+//       192^2 x 4, seven jobs, and x 5 one, 15 % / 42 % of the work: 0.88 / 1.67
+//       ms in teams, 0.96 / 1.46 as launches; x 4 and x 5 a job each, 24 % / 55
+//       %: 1.09 / 0.88 against 1.20 / 0.79
+//   mixed sizes     ... at most half: of 70 calls of 9 to 64 uneven jobs, 64^2
+//       to 256^2 x 1 to 5, teams took 0.57 to 1.02 times the launches' time
+//       where less than a third of the work was 192^2 and 0.7 to 1.1 where a
+//       third to a half was, but for three of 11 and 17 jobs that fill the XCDs
+//       badly (1.04 to 1.26); from a half on 0.8 to 1.33
+// Jobs that no team holds (256^2 x 7 and 8) run as launches after the teams'
+// if they are at most a third of the work (256^2 x 3, seven jobs, and x 8 one,
+// 28 %: 1.32 ms, all as launches 1.47; three jobs and one, 47 %: 1.30, 1.12).
 static void choose_team(const JobRec* jobs, int njobs, const Tuning* force, std::vector<char>& team) {
-  double work = 0.0, unsuited = 0.0;
+  double work = 0.0, unsuited = 0.0, misfit = 0.0;
   bool mixed = false;
   int maxN = 0, maxM = 1;  // the launches take the tuning of the largest
   for (int b = 0; b < njobs; ++b) {
@@ -1531,7 +1544,12 @@ static void choose_team(const JobRec* jobs, int njobs, const Tuning* force, std:
   std::vector<char> free_choice(njobs, 0);
   for (int b = 0; b < njobs; ++b) {
     const JobRec& jb = jobs[b];
-    if (!team_fits(jb.N, jb.M)) continue;
+    const double w = (double)jb.J * jb.T * jb.M * jb.N * jb.N;
+    if (!team_fits(jb.N, jb.M)) {
+      misfit += w;
+      work += w;
+      continue;
+    }
     const int route = get_route(jb.N, jb.M, njobs);
     if (asked || route == MRPIE_ROUTE_LAUNCHES) {
       const int most = force ? force->lds_sweep : get_tuning(jb.N, jb.M, njobs).lds_sweep;
@@ -1543,15 +1561,13 @@ static void choose_team(const JobRec* jobs, int njobs, const Tuning* force, std:
       continue;
     }
     free_choice[b] = 1;
-    team[b] = team_suits(jb.N, jb.M, njobs);
     mixed |= jb.N != jobs[0].N;
-    const double w = (double)jb.J * jb.T * jb.M * jb.N * jb.N;
     work += w;
-    if (!team[b]) unsuited += w;
+    if (!team_suits(jb.N, jb.M, njobs)) unsuited += w;
   }
-  if (!mixed) return;
+  const bool teams = 3.0 * misfit <= work && (mixed ? 2.0 : 3.0) * (unsuited + misfit) <= work;
   for (int b = 0; b < njobs; ++b)
-    if (free_choice[b]) team[b] = 2.0 * unsuited <= work;
+    if (free_choice[b]) team[b] = teams;
 }
 
 // Jobs go to the teams (one persistent launch) or through the row / column

@@ -81,3 +81,23 @@ def test_installed_route_decides(N, M):
     for g in (a, b):
         assert rel_l2(g["O"], o["O"]) < 1e-4 and rel_l2(g["P"], o["P"]) < 1e-4 and g["status"] == 0
     assert rel_l2(a["O"], b["O"]) < 1e-5 and np.allclose(a["err"], b["err"], rtol=1e-5, atol=0)
+
+
+@pytest.mark.parametrize("N,modes,J,want", [
+    (192, (4, 5), (6, 6), {"k_rows"}), (192, (4,) * 7 + (5,), (6,) * 8, {"k_team"}),
+    (192, (3, 3, 5, 5), (6,) * 4, {"k_rows"}), (256, (3, 5), (4, 4), {"k_rows"}),
+    (256, (3, 8), (4, 4), {"k_rows"}), (256, (3,) * 7 + (8,), (3,) * 8, {"k_team", "k_rows"}),
+    (256, (3, 3, 8), (4, 4, 1), {"k_team", "k_rows"})])
+def test_jobs_of_a_call_run_one_way_together(N, modes, J, want):
+    """Jobs of which some suit the persistent launch and some do not, and jobs
+    that it does not hold: one route by most of the work, two only where few
+    are left over."""
+    ws = [wl.small_case(950 + b, N + 19, N, M, j, W=N + 26, name=f"t{b}") for b, (M, j) in enumerate(zip(modes, J))]
+    prm = dict(EPIE, iterations=2)
+    jobs, kernels = ran(lambda: batch(ws, **prm))
+    assert kernels & {"k_team", "k_rows"} == want
+    for j, w in zip(jobs, ws):
+        o = run_oracle(w, prm)
+        assert rel_l2(j["obj"].cpu().numpy(), o["O"]) < 1e-4
+        assert rel_l2(j["probe"].cpu().numpy(), o["P"]) < 1e-4
+        assert int(j["status"].item()) == 0
