@@ -254,9 +254,10 @@ int mrpie_get_route(int32_t N, int32_t M, int32_t batched, int32_t* route);
  * `njobs` independent reconstructions of any mix of N, M, J and object
  * size.  By default most calls run as one persistent launch: the workgroups
  * of each XCD form teams that take jobs from a queue, largest first, and run
- * each from its first position to its last.  The others (probes of 192^2 in
- * large numbers, 7 or 8 modes, installed or passed tunings) advance lock-step
- * by position: every launch advances one position of every
+ * each from its first position to its last.  The others advance lock-step by
+ * position (probes of 192^2 alone, in more than 8 jobs or of more than 4 modes,
+ * 256^2 of 5 or 6 modes in fewer than 3 jobs and of 7 or 8 modes, calls of mixed
+ * sizes that are mostly such work, installed or passed tunings): every launch advances one position of every
  * running job, so one pair of launches carries the work of many jobs.  The
  * jobs of a stream run in at most 36 launch lanes (the job table of one
  * launch); a share of more than 36 jobs is dealt to the lanes longest job

@@ -90,7 +90,8 @@ def _job_array(jobs, prm):
 
 
 def rpie_batched(jobs, stream=None, tuning=None, **params):
-    """Run independent M-rPIE reconstructions lock-step in shared launches.
+    """Run independent M-rPIE reconstructions in one persistent launch or
+    lock-step in shared launches.
 
     jobs: list of dicts with GPU tensors obj, probe, pos, intens and optional
     err, status, workspace.  Keyword arguments are the shared mrpie_params;
@@ -250,7 +251,7 @@ def validate(problem: Problem, **params) -> int:
     return lib.mrpie_validate(C.byref(problem), C.byref(prm))
 
 
-TIMED_KERNELS = ("k_rows", "k_cols", "k_reg_cols", "k_reg_gemm1", "k_adj_p3", "k_lds_sweep", "k_upd", "k_gat",
+TIMED_KERNELS = ("k_rows", "k_cols", "k_reg_cols", "k_reg_gemm1", "k_adj_p3", "(unused)", "k_upd", "k_gat",
                  "k_team")
 
 

@@ -36,7 +36,7 @@ inline int n_index(int N) {
   }
 }
 
-// Roots of unity w_N^e = exp(-2 pi i e / N), e < N, for the four sizes;
+// Roots of unity w_N^e = exp(-2 pi i e / N), e < N, for the five sizes;
 // written by k_init_twiddles in double precision and rounded once.  Each
 // translation unit holds its own copy (no relocatable device code).
 static __device__ float2 g_tw[5][256];
@@ -201,7 +201,7 @@ std::mutex& side_mutex();
 // a start / stop event pair, so the events carry that dispatch's own start
 // and end time on its stream; mrpie_timing_read() averages them.
 enum TimedKernel {
-  TK_ROWS = 0, TK_COLS = 1, TK_REG = 2, TK_GEMM = 3, TK_ADJ = 4, TK_LDS = 5, TK_UPD = 6, TK_GAT = 7, TK_TEAM = 8, TK_COUNT = 9
+  TK_ROWS = 0, TK_COLS = 1, TK_REG = 2, TK_GEMM = 3, TK_ADJ = 4, TK_UNUSED = 5, TK_UPD = 6, TK_GAT = 7, TK_TEAM = 8, TK_COUNT = 9
 };
 struct TimedLaunch {
   hipEvent_t start = nullptr, stop = nullptr;

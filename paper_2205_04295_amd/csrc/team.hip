@@ -44,7 +44,7 @@
 // of the workgroups that have arrived when its leader closes the list (all of
 // them as a rule; the leader waits up to 10 ms for stragglers), later ones
 // leave at once.  A team that came out too small for its job's units runs the
-// job in loops over them (run_loops), slowly but to the same end.
+// job in loops over them (run_loops), slowly but to the same bits.
 #include <algorithm>
 #include <mutex>
 #include <vector>
@@ -1329,12 +1329,22 @@ int record_turn(Turns& t, int from, int n, int nxcc, hipStream_t s) {
 
 // Whether a call of `njobs` jobs, of this size each, is for the teams rather
 // than the launches of sweep.hip.  Measured in us a position of the card
-// (launches / team): a single 64^2 x 1 9.8 / 6.1, 128^2 x 3 11.7 / 8.3,
-// 256^2 x 3 14.9 / 14.3, 256^2 x 4 18.2 / 17.0, but 256^2 x 5 21.2 / 26.4 (its
-// waves take three modes each and spill) and 192^2 x 3 13.9 / 15.1 (48 units
-// of 12 points a lane leave half of the vector units idle); 8 jobs of 256^2 x
-// 3 4.1 / 2.1, x 5 5.6 / 3.8, of 192^2 x 3 3.0 / 2.2; 40 jobs of 256^2 x 3
-// 2.6 / 2.1, x 5 4.4 / 3.8, of 192^2 x 3 1.6 / 2.2, of 128^2 x 3 0.8 / 0.8.
+// (launches / team), whole calls of 8 to 64 positions a job, every M from 1 to
+// 8 and 1 to 64 jobs:
+//   32^2, 64^2, 128^2  teams faster throughout: singles 64^2 x 1 10.2 / 6.8,
+//       128^2 x 3 12.2 / 9.0, x 8 17.5 / 12.6; least at 20 to 64 jobs of 128^2
+//       with many modes: 40 x 5 1.71 / 1.53, 64 x 5 1.70 / 1.61
+//   256^2  x 3: single 16.3 / 14.6, 8 jobs 4.23 / 1.92, 9 3.79 / 3.29 (two to a
+//       team on one XCD), 40 3.22 / 2.72; x 4: single 18.3 / 17.5; x 5 and x 6
+//       (waves take three modes and spill): single 21.6 / 25.0 and 23.2 / 27.3,
+//       2 jobs 14.2 / 12.6, 3 10.1 / 8.4, 9 6.37 / 5.86, 20 4.72 / 4.68
+//   192^2  (48 units of 12 points a lane leave CUs idle)  single x 3 14.4 /
+//       16.2; x 3 2 jobs 9.8 / 8.2, 8 3.13 / 2.11, 9 2.89 / 3.85, 16 2.25 / 2.27,
+//       32 1.92 / 2.42; x 4 8 3.58 / 2.34, 9 3.33 / 3.97; x 5 2 12.5 / 13.9, 5
+//       5.52 / 5.70, 8 4.18 / 3.56, 9 3.80 / 6.09.  (Up to 16 jobs x 2 and up to
+//       32 x 1 the teams would win as well: 16 x 2 1.94 / 1.25, 32 x 1 1.13 /
+//       0.71; two 256^2 x 5 and 8 jobs of 192^2 x 5 likewise.)
+// For calls of mixed sizes see choose_team.
 bool team_suits(int N, int M, int njobs) {
   if (N == 192) return M <= 4 && njobs >= 2 && njobs <= 8;
   if (N == 256) return M <= 4 || (M <= 6 && njobs > 2);

@@ -2,9 +2,12 @@
 
 A call of the sweep is a fixed sequence of launches on one stream with no
 allocation, no synchronisation and no memset (fills are kernels), so it can
-be recorded once and replayed: the replay issues the whole lock-step sweep
-(two launches per position and tick, for every job) as one graph launch.
-Each replay continues the reconstruction from the current buffer contents.
+be recorded once and replayed: the replay issues its persistent launch, or
+the whole lock-step sweep (two or three launches per position and tick, for
+every job), as one graph launch.  Each replay continues the reconstruction
+from the current buffer contents.  Replays on several streams at once do not
+wait for each other's XCDs (an eager call does): persistent launches of two
+graphs on the same XCDs give the same results, slowly.
 """
 from __future__ import annotations
 

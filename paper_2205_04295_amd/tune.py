@@ -37,6 +37,7 @@ CANDIDATES = [dict(rows_radix=rr, cols_radix=cr, rows_threads=th, lds_sweep=0, c
                    rows_split=sp)
               for rr in (4, 8) for cr in (4, 8) for th in (256, 512) for cw in (1, 4) for ip in (0, 1)
               for sp in (0, 1)]
+# the persistent launch as a tuning asks for it, where lds_fits(N, M)
 LDS_CANDIDATE = dict(rows_radix=8, cols_radix=8, rows_threads=256, lds_sweep=8, cols_width=1, rows_inplace=0,
                      rows_split=0)
 
@@ -47,8 +48,8 @@ def call_class(jobs):
 
 
 def lds_fits(N, M):
-    """True when the M modes of an N x N probe fit the LDS together (a
-    tuning's lds_sweep applies)."""
+    """True when the M modes of an N x N probe fit one workgroup's LDS together:
+    a tuning whose lds_sweep is M or more then takes the persistent launch."""
     return N <= 128 and M * N * N <= 16384
 
 
