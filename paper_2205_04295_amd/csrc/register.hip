@@ -657,14 +657,25 @@ int reg_window(int up, int* U, int* c) {
 }
 
 // The folded products need windows that fill their tiles of 16 + 16 samples.
-constexpr int kFoldMinU = 32;
+// In the plain products' workspace they may take fewer pairs a pass, and a pass
+// more is some 10 launches: calls of fewer than so many U N (N + U) of all pairs
+// then keep the plain products (3.5e8, 1e8 for windows above 320 samples, whose
+// plain products are the slower ones).  Measured, us plain / folded in more
+// passes: 64^2 3 pairs at upsample 100 77 / 117, 67 pairs at 37 87 / 134, 128^2
+// 30 at 100 136 / 158, 256^2 10 at 100 181 / 208, 3.2e8: 256^2 30 at 75 231 /
+// 248; 4.3e8: 256^2 67 at 50 341 / 334, 1.0e9: 67 at 100 440 / 338; windows above
+// 320: 32^2 10 pairs at 214 81 / 98, 64^2 10 at 214 109 / 121, 30 at 214 (2.4e8)
+// 145 / 129.  In as many passes the folded ones win: 64^2 3 at 333 101 / 76,
+// 128^2 1 at 75 99 / 79, 256^2 1 at 100 160 / 100.
+constexpr int kFoldMinU = 32, kWideU = 320;
+constexpr double kFoldMinWork = 3.5e8, kFoldMinWorkWide = 1e8;
 
 RegLayout reg_layout(int N, int B, int up) {
   RegLayout L{};
   int U, c;
   reg_window(up, &U, &c);
   const int chunk = std::max(1, std::min(B, kRegChunk));
-  const int t2 = U > 320 ? 64 : 32;  // (windows above 320 are always folded)
+  const int t2 = U > kWideU ? 64 : 32;
   int tiles = ((U + t2 - 1) / t2) * ((U + t2 - 1) / t2);
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = ws_align(off + bytes); return o; };
@@ -682,12 +693,23 @@ RegLayout reg_layout(int N, int B, int up) {
     L.F = take((size_t)n * f);
   };
   const size_t plain = (size_t)U * N * 16;
-  place(chunk, plain, plain, 0);
+  const auto plain_products = [&] {
+    place(chunk, plain, plain, 0);
+    // (The workspace counts the maxima of windows above 320 by 64 x 64 tiles,
+    // the kernels take 32 x 32: theirs lie over the spectra, which the second
+    // product does not read.)
+    if (U > kWideU) {
+      const size_t n = (size_t)((U + 31) / 32) * ((U + 31) / 32) * chunk;
+      L.tile_v = L.work;
+      L.tile_i = L.work + ws_align(n * 8);
+    }
+  };
+  plain_products();
   L.total = off;
   if (U < kFoldMinU) return L;
   // The folded products lay out less for the table and more for each pair.
   // They take no more memory than the plain ones: fewer pairs a pass if need
-  // be, down to half (few pairs of a small window stay with the plain GEMMs).
+  // be, down to half.
   const int ct = c / 16 + 1, plain_tiles = tiles;
   const size_t lanes = (size_t)(N / 4 + 1) * 64;            // Fold<N>::TILE
   const size_t behind = (N / 16 + 1) - N * N / lanes;       // Fold<N>::RT - HOME
@@ -696,13 +718,15 @@ RegLayout reg_layout(int N, int B, int up) {
   int n = chunk;
   do place(n, ct * lanes * 8, 2 * ct * lanes * 16, behind * lanes * 16);
   while (off > L.total && --n);
-  if (2 * n < chunk || n == 0) {
+  const int passes = n ? (B + n - 1) / n : 0;  // of like size
+  if (2 * n < chunk || n == 0 ||
+      (passes > (B + chunk - 1) / chunk &&
+       (double)B * U * N * (N + U) < (U > kWideU ? kFoldMinWorkWide : kFoldMinWork))) {
     tiles = plain_tiles;
     L.fold = false;
-    place(chunk, plain, plain, 0);
+    plain_products();
     return L;
   }
-  const int passes = (B + n - 1) / n;  // of like size
   place(std::max(1, (B + passes - 1) / passes), ct * lanes * 8, 2 * ct * lanes * 16, behind * lanes * 16);
   return L;
 }
@@ -747,13 +771,13 @@ static int register_impl(int B, const float2* ref, const float2* mov, int up, in
       hipLaunchKernelGGL(k_reg_fold<N>, dim3((kSlots + 255) / 256, nb), dim3(256), 0, s, a);
       FoldWork w{(Fold<N>::RT + 1) / 2, (ct + JT - 1) / JT, ct, 0};
       w.waves = nb * w.rows * w.cols;
-      launch_k(TK_GEMM, k_reg_fold1<N>, dim3((w.waves + 3) / 4), dim3(256), 0, s, a, w);
+      launch_ku(TK_GEMM, nb, k_reg_fold1<N>, dim3((w.waves + 3) / 4), dim3(256), 0, s, a, w);
       w.rows = ct;
       tiles = w.rows * w.cols;
       w.waves = nb * tiles;
       hipLaunchKernelGGL(k_reg_fold2<N>, dim3((w.waves + 3) / 4), dim3(256), 0, s, a, w);
     } else {
-      launch_k(TK_GEMM, k_reg_gemm1<N>, dim3((N + G1_TX - 1) / G1_TX, gt, nb), dim3(256), 0, s, a);
+      launch_ku(TK_GEMM, nb, k_reg_gemm1<N>, dim3((N + G1_TX - 1) / G1_TX, gt, nb), dim3(256), 0, s, a);
       hipLaunchKernelGGL(k_reg_gemm2<N>, dim3(gt, gt, nb), dim3(256), 0, s, a);
     }
     hipLaunchKernelGGL(k_reg_final, dim3(nb), dim3(64), 0, s, a, tiles);
