@@ -283,6 +283,7 @@ struct JobBarrier {
   Glob flags;
   int rank, size;
   Shared* sh;
+  int spin;            // (TeamArgs)
   unsigned epoch = 0;  // positions begun
   __device__ __forceinline__ float operator()(int b) const {
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
@@ -301,7 +302,7 @@ struct JobBarrier {
         for (;;) {
           v = one.ld_team<unsigned long long>();
           if (__builtin_amdgcn_ballot_w64((int)((unsigned)v - epoch) >= 0) == ~0ull) break;
-          if (wall_clock64() - t0 > __builtin_amdgcn_readfirstlane(sh->spin)) {
+          if (wall_clock64() - t0 > spin) {
             sh->ok = 0;
             break;
           }
@@ -446,7 +447,7 @@ __device__ __forceinline__ void run_units(const Common& cm, const JobRec& jb, fl
   F f;
   init_fft<N>(f, (float2*)(lds0 + TeamLds<N, WV>::kPat));
 
-  JobBarrier<WV> barrier{flags, rank, size, sh};
+  JobBarrier<WV> barrier{flags, rank, size, sh, __builtin_amdgcn_readfirstlane(sh->spin)};
   // The spectra a wave holds as rows (element i: row r, column l + L i) and
   // as columns (row l + L i, column c).
   auto ex_row = [&](int p, unsigned r, unsigned l, int i) __attribute__((always_inline)) {
@@ -821,7 +822,7 @@ __device__ __forceinline__ void run_loops(const Common& cm, const JobRec& jb, fl
   const Glob gobj(jb.obj), gprobe(jb.probe), gpos(jb.pos), gI(jb.I), ws(jb.ws);
   const Glob psi = ws.far(ly.psi[0]), gerr = ws.far(ly.err), gis = ws.far(ly.isum);
   const Glob shares = ws.far(ly.patch[0]);  // a lane's share of a unit's error and intensity
-  JobBarrier<WV> barrier{ws.far(ly.psi[1] + kFlagOffset), rank, size, sh};
+  JobBarrier<WV> barrier{ws.far(ly.psi[1] + kFlagOffset), rank, size, sh, __builtin_amdgcn_readfirstlane(sh->spin)};
   char* const lds0 = lds;
   float2* const wsc = (float2*)(lds + TeamLds<N, WV>::kHead) + wave * F::SCRATCH;
   F f;
