@@ -1221,8 +1221,11 @@ int job_need(int N, int M, int waves, int km) {
   while (uw * 2 * mw <= waves) uw *= 2;
   return (N / G + uw - 1) / uw;
 }
-// Members that take part in it: as many as its units keep busy (Deal's).
+// Members that take part in it: as many as its units keep busy (Deal's); but
+// 32^2 x 1 is one workgroup's (5.65 us a position, by two 5.95; x 2 6.57 / 6.35,
+// 64^2 x 1 by one 9.67, by eight 6.40).
 int job_members(int N, int M, int waves, int km) {
+  if (N == 32 && M == 1) return 1;
   const int G = N == 256 ? 2 : N == 192 || N == 128 ? 4 : N == 64 ? 8 : 16, mw = (M + km - 1) / km;
   int uw = 1;
   while (uw * 2 * mw <= waves && uw * kMaxSize < N / G) uw *= 2;

@@ -79,3 +79,24 @@ def test_wait_that_gives_up(N, M, jobs, members):
         assert a["status"] == 4 or (a["status"] == 0 and np.array_equal(a["O"], b["O"]))
     for a, b in zip(team(ws, members, **prm), ref):
         assert a["status"] == 0 and np.array_equal(a["O"], b["O"]) and np.array_equal(a["P"], b["P"])
+
+
+def test_single_32_is_one_workgroup():
+    """32^2 x 1 alone runs as a team of one; more jobs, and more modes, by two
+    members each: the same bits."""
+    from paper_2205_04295_amd import api
+    for M in (1, 2):
+        w = wl.small_case(880, 71, 32, M, 40, W=60, name="u")
+        prm = dict(EPIE, iterations=3)
+        many = team([w] * 9, 32, **prm)
+        one = team([w], 32, **prm)[0]
+        for members in (1, 2):
+            g = team([w], members, **prm)[0]
+            assert np.array_equal(g["O"], one["O"]) and np.array_equal(g["P"], one["P"])
+            assert np.array_equal(g["err"], one["err"])
+        for g in many:
+            assert np.array_equal(g["O"], one["O"]) and np.array_equal(g["err"], one["err"])
+        d = to_dev(w)
+        api.rpie(d["obj"], d["probe"], d["pos"], d["I"], **prm)
+        torch.cuda.synchronize()
+        assert np.array_equal(d["obj"].cpu().numpy(), one["O"])
