@@ -7,8 +7,9 @@
 //
 //   k_cols  (step s):   one workgroup per detector column, all modes:
 //                       forward column FFT, mode-summed modulus replacement
-//                       (Eq. 7), inverse column FFT, in place in psi[s&1];
-//                       accumulates the Fourier error.
+//                       (Eq. 7), inverse column FFT, in place in psi[s&1]
+//                       (a single sweep: from psi[1], where its row pass
+//                       writes, to psi[0]); accumulates the Fourier error.
 //   k_rows  (s-1 -> s): one workgroup per probe row r: inverse row FFTs of
 //                       psi[(s-1)&1]; probe update of row r (Eq. 5); object
 //                       update (Eq. 6) of the box rows that are rows of the
@@ -16,7 +17,8 @@
 //                       box, exit waves P_p o (Eq. 1/4) and forward row FFTs
 //                       into psi[s&1].
 //
-// Probe, patch and spectra are double-buffered by step parity, so inside a
+// Probe, patch and spectra are double-buffered by step parity (a single
+// sweep's spectra by layout, see sidx), so inside a
 // k_rows launch every buffer a workgroup reads is disjoint from every buffer
 // any workgroup writes; the object rows a workgroup writes are exactly the
 // rows it then re-gathers (merged from LDS).  The sweep has no atomics on
@@ -62,7 +64,11 @@ __device__ __forceinline__ size_t pick(const size_t (&a)[2], int i) { return i ?
 // row pass writes its row transforms tiled and the column pass reads them
 // tiled (column pass 6.1 -> 5.6 us, row pass 8.5 -> 8.8 us at 256^2 x 3);
 // the column pass writes its results row-major, which the next row pass
-// reads in whole lines (tiled reads there cost more than they saved).
+// reads in whole lines (tiled reads there cost more than they saved).  The
+// two layouts lie in a buffer each, psi[1] and psi[0]: in one buffer a column
+// workgroup's results would overwrite elements that a workgroup which starts
+// late has still to read (with the launches timed, up to two fifths of the
+// 32^2 x 1 sweeps came out wrong).
 constexpr int kTileCols = 8;
 template <int N, bool TILE>
 __device__ __forceinline__ size_t sidx(int k, int c) {
@@ -93,7 +99,7 @@ __device__ __forceinline__ void rows_body(const Common& cm, const JobRec& jb, in
   float2* bufB = IP ? bufA + M * PT : bufA + 2 * M * PT;  // forward-FFT partner (IP: inside bufA)
   __shared__ float redf[32];
 
-  const float2* psi_prev = (const float2*)(ws + pick(L.psi, prv));
+  const float2* psi_prev = (const float2*)(ws + pick(L.psi, SINGLE ? 0 : prv));
   const float2* patch_prev = (const float2*)(ws + pick(L.patch, prv));
   const float2* Pold = prv == 0 ? jb.probe : (const float2*)(ws + L.probe1);
   float2* Pnew = cur == 0 ? jb.probe : (float2*)(ws + L.probe1);
@@ -287,7 +293,7 @@ __device__ __forceinline__ void rows_body(const Common& cm, const JobRec& jb, in
     ((float*)(ws + pick(L.omax, cur)))[r] = om;
     ((float*)(ws + pick(L.pmax, cur)))[r] = pm;
   }
-  float2* dst = (float2*)(ws + pick(L.psi, cur));
+  float2* dst = (float2*)(ws + pick(L.psi, SINGLE ? 1 : cur));
   fft_lds_store<N, false, R4, 0, PT, PAD>(bufA, bufB, M, tw, [&](int p, int cc, float2 v) {
     dst[p * NN + sidx<N, SINGLE>(r, cc)] = v;
   });
@@ -495,7 +501,8 @@ __device__ __forceinline__ void cols_body(const JobRec& jb, int t, float2* smem)
   const int it = t / jb.J, jn = t - it * jb.J;
   const WsLayout L = ws_layout(N, M, jb.T);
   const size_t NN = (size_t)N * N;
-  float2* psi = (float2*)(jb.ws + pick(L.psi, t & 1));
+  const float2* psi = (const float2*)(jb.ws + pick(L.psi, TILE ? 1 : t & 1));
+  float2* out = (float2*)(jb.ws + pick(L.psi, TILE ? 0 : t & 1));
   const float* Ij = jb.I + (size_t)jn * NN;
   constexpr int NT = 256;               // threads
   constexpr int PIX = (N * CW + NT - 1) / NT;  // detector pixels per thread
@@ -594,7 +601,7 @@ __device__ __forceinline__ void cols_body(const JobRec& jb, int t, float2* smem)
       const size_t off = (size_t)k * N + u0 + c;
 #pragma unroll
       for (int p = 0; p < MM; ++p)
-        if (p < M) psi[p * NN + sidx<N, false>(k, u0 + c)] = H[(p * CW + c) * PT + k];
+        if (p < M) out[p * NN + sidx<N, false>(k, u0 + c)] = H[(p * CW + c) * PT + k];
     }
   }
   e = wave_sum(e);
@@ -628,7 +635,8 @@ __device__ __forceinline__ void cols_body_rd(const JobRec& jb, int t, float2* sm
   const int it = t / jb.J, jn = t - it * jb.J;
   const WsLayout L = ws_layout(N, M, jb.T);
   const size_t NN = (size_t)N * N;
-  float2* psi = (float2*)(jb.ws + pick(L.psi, t & 1));
+  const float2* psi = (const float2*)(jb.ws + pick(L.psi, TILE ? 1 : t & 1));
+  float2* out = (float2*)(jb.ws + pick(L.psi, TILE ? 0 : t & 1));
   const float* Ij = jb.I + (size_t)jn * NN;
   const int tid = threadIdx.x;
 
@@ -725,7 +733,7 @@ __device__ __forceinline__ void cols_body_rd(const JobRec& jb, int t, float2* sm
     }
     dftR<R0, true>(v);
 #pragma unroll
-    for (int r = 0; r < R0; ++r) psi[p0 * NN + sidx<N, false>(j0 + Q0 * r, u)] = v[r];
+    for (int r = 0; r < R0; ++r) out[p0 * NN + sidx<N, false>(j0 + Q0 * r, u)] = v[r];
   }
   e = wave_sum(e);
   isv = wave_sum(isv);
